@@ -2812,15 +2812,36 @@ fea_status fea_focal_vote(fea_ctx* c, int32_t n_cams, int64_t n_pairs, const int
     lst[fill[gi]++] = (int32_t)p;
     if (gj != gi) lst[fill[gj]++] = (int32_t)p;
   }
+  // the focal length amid the candidates that the rank-2 forms are scaled at
+  const auto [f_lo, f_hi] = std::minmax_element(cand_f, cand_f + n_cand);
+  const double f0 = *f_hi < 1e15 * *f_lo && *f_hi < 1e30 && *f_lo > 1e-30 ? std::sqrt(*f_lo) * std::sqrt(*f_hi) : 0.0;
+  // work items: runs of a group's entries, one at least per group
+  const int64_t n_ent = (int64_t)lst.size();
+  const int64_t chunk = fea::fv_items_chunk(n_ent, n_cand);
+  std::vector<int2> items;
+  std::vector<int32_t> ioff((size_t)G + 1), eg((size_t)n_ent);
+  for (int32_t g = 0; g < G; ++g) {
+    ioff[g] = (int32_t)items.size();
+    for (int64_t x = off[g]; x == off[g] || x < off[g + 1]; x += chunk)
+      items.push_back(make_int2((int)x, (int)std::min<int64_t>(x + chunk, off[g + 1])));
+    std::fill(eg.begin() + off[g], eg.begin() + off[g + 1], g);
+  }
+  ioff[G] = (int32_t)items.size();
   DeviceGuard dg(c->device);
   CallScratch sc(c->stream);
-  int32_t *dpi, *dpj, *dgrp, *doff, *dlst, *dkb;
-  double *dF, *dfc, *dcand, *dvotes, *dfb;
+  int32_t *dpi, *dpj, *dgrp, *dioff, *dlst, *deg, *dkb;
+  int2* ditems;
+  uint8_t* dent;
+  double *dF, *dfc, *dcand, *dpart = nullptr, *dvotes, *dfb;
   HIP_OR_FAIL(c, sc.put(dpi, pair_i, (size_t)n_pairs));
   HIP_OR_FAIL(c, sc.put(dpj, pair_j, (size_t)n_pairs));
   HIP_OR_FAIL(c, sc.put(dgrp, grp.data(), grp.size()));
-  HIP_OR_FAIL(c, sc.put(doff, off.data(), off.size()));
+  HIP_OR_FAIL(c, sc.put(dioff, ioff.data(), ioff.size()));
   HIP_OR_FAIL(c, sc.put(dlst, lst.data(), lst.size()));
+  HIP_OR_FAIL(c, sc.put(deg, eg.data(), eg.size()));
+  HIP_OR_FAIL(c, sc.put(ditems, items.data(), items.size()));
+  HIP_OR_FAIL(c, sc.alloc(dent, (size_t)n_ent * fea::fv_entry_bytes()));
+  if ((int32_t)items.size() != G) HIP_OR_FAIL(c, sc.alloc(dpart, items.size() * (size_t)n_cand));
   HIP_OR_FAIL(c, sc.put(dF, F, (size_t)9 * n_pairs));
   HIP_OR_FAIL(c, sc.put(dfc, fc.data(), fc.size()));
   HIP_OR_FAIL(c, sc.put(dcand, cand_f, (size_t)n_cand));
@@ -2832,8 +2853,8 @@ fea_status fea_focal_vote(fea_ctx* c, int32_t n_cams, int64_t n_pairs, const int
     HIP_OR_FAIL(c, hipEventCreate(&ev[0]));
     HIP_OR_FAIL(c, hipEventCreate(&ev[1]));
   }
-  hipError_t e = fea::launch_fv_vote(c->stream, G, n_cand, doff, dlst, dpi, dpj, dgrp, dF, dfc, dcand, tau, dvotes,
-                                     ev[0], ev[1]);
+  hipError_t e = fea::launch_fv_vote(c->stream, G, (int)items.size(), n_ent, n_cand, deg, dlst, ditems, dioff, dpi,
+                                     dpj, dgrp, dF, dfc, dcand, f0, tau, dent, dpart, dvotes, ev[0], ev[1]);
   if (e == hipSuccess) e = fea::launch_fv_best(c->stream, G, n_cand, dvotes, dcand, dfb, dkb);
   if (e == hipSuccess) e = fetch(c->stream, f_best, dfb, (size_t)G);
   if (e == hipSuccess) e = fetch(c->stream, k_best, dkb, (size_t)G);
