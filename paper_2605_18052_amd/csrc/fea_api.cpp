@@ -121,10 +121,13 @@ hipError_t download(fea_ctx* c, std::vector<T>& dst, const DBuf& b, size_t n) {
 std::vector<DBuf*> all_bufs(fea_ctx* c) {
   std::vector<DBuf*> v;
   for (int b = 0; b < 3; ++b) {
-    for (int a = 0; a < 4; ++a) v.push_back(&c->lay[b][a]);
+    if (b == 0)
+      for (int a = 0; a < 4; ++a) v.push_back(&c->lay[b][a]);
+    else
+      v.push_back(&c->lay_block[b]);
     v.push_back(&c->lpos[b]);
   }
-  DBuf* one[] = {&c->perm, &c->swp, &c->item_rec, &c->d_scene_item_off, &c->scene_loss, &c->pair_item_off,
+  DBuf* one[] = {&c->seg_ws, &c->perm, &c->swp, &c->item_rec, &c->d_scene_item_off, &c->scene_loss, &c->pair_item_off,
                  &c->item_keep, &c->item_base, &c->part, &c->d_pair_i, &c->d_pair_j, &c->d_cam_off,
                  &c->d_cam_ent, &c->d_group, &c->d_grp_off, &c->d_grp_cams, &c->d_cx, &c->d_cy, &c->a6,
                  &c->tp, &c->logf, &c->m_a6, &c->v_a6, &c->m_t, &c->v_t, &c->m_f, &c->v_f, &c->R[0],
@@ -531,13 +534,10 @@ fea_status load_matches_common(fea_ctx* c, int64_t n, const float* x1, const flo
   if (bad & fea::kErrSameCam) return fail(c, FEA_EINVAL, "a match has cam1 == cam2");
   if (bad & fea::kErrNonFinite) return fail(c, FEA_ENONFINITE, "a keypoint coordinate is not finite");
   if (c->layout_len >= (int64_t)1 << 31) return fail(c, FEA_EINVAL, "too many matches for 32-bit offsets");
-  // pristine full layout lives in buffer 0; buffers 1 and 2 take the
-  // filtered layouts of successive rounds
-  for (int b = 1; b < 3; ++b) {
-    for (int a = 0; a < 4; ++a)
-      HIP_OR_FAIL(c, dalloc(c->lay[b][a], std::max<int64_t>(c->layout_len, 1) * sizeof(float)));
-    HIP_OR_FAIL(c, dalloc(c->lpos[b], std::max<int64_t>(c->layout_len, 1) * sizeof(int32_t)));
-  }
+  // pristine full layout lives in buffer 0; buffers 1 and 2 (allocated with
+  // it) take the filtered layouts of successive rounds.  Steps captured on
+  // earlier buffers are out of date: fea_init_poses, which has to come next,
+  // drops them
   // every pair must lie inside one scene
   c->pair_scene.assign(c->P, 0);
   for (int64_t k = 0; k < c->P; ++k) {

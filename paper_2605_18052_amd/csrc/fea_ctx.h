@@ -91,7 +91,11 @@ struct fea_ctx {
   int32_t n_logged = 0;
 
   // device buffers
-  fea::DBuf lay[3][4];   // x1, y1, x2, y2 (fp32): [0] full layout, [1]/[2] filtered (ping-pong)
+  fea::DBuf lay[3][4];   // x1, y1, x2, y2 (fp32): [0] full layout, [1]/[2] filtered (ping-pong; views
+                         // into lay_block)
+  fea::DBuf lay_block[3];  // [1]/[2]: the filtered layouts' coordinates, one block each (the sort's
+                           // records and keys while matches are loaded)
+  fea::DBuf seg_ws;      // int32: digit counts, tile counts and scan scratch of the sort
   fea::DBuf lpos[3];     // int32: sorted position of each layout entry (-1 = padding)
   fea::DBuf perm;        // int32 [M] input index of each sorted position
   fea::DBuf swp;         // uint8 [M]

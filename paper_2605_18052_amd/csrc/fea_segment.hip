@@ -5,6 +5,18 @@
 // adjustment iterations (FastMap, Experiments: marshalling done on the GPU
 // with tensor indexing); here every step is an integer kernel so the result
 // is bit-exact and deterministic.
+//
+// All of it is bound by memory.  The matches arrive in any order, so one
+// pass has to reach into memory at random: validation packs each match's
+// four coordinates, already in the pair's orientation, into one 16-byte
+// record, so that the gather after the sort makes one random access per
+// match instead of six of 4 bytes (30M matches in random order, 1,000
+// cameras: gather 3,447 -> 821 us).  The sort moves 8 bytes per match and
+// pass (key; input index with the swap flag in its top bit) and takes the
+// fewest passes of at most 8 bits; a tile of 4,096 keys is first sorted in
+// LDS so that a digit's keys leave as one run (five 4-bit passes 2,070 ->
+// three 7-bit passes 590 us).  Records and keys live in the two buffers
+// that hold the filtered layouts of later rounds and are free until then.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -20,11 +32,15 @@ namespace {
 constexpr int kScanThreads = 256;
 constexpr int kScanPer = 8;
 constexpr int kScanTile = kScanThreads * kScanPer;
-constexpr int kRadixBits = 4;
-constexpr int kRadixBins = 1 << kRadixBits;
+constexpr int kMaxRadixBits = 8;
+constexpr int kMaxRadixBins = 1 << kMaxRadixBits;
 constexpr int kRsThreads = 256;
-constexpr int kRsPer = 8;
+constexpr int kRsWaves = kRsThreads / kWave;
+constexpr int kRsPer = 16;
 constexpr int kRsTile = kRsThreads * kRsPer;
+constexpr int kRsWaveTile = kRsPer * kWave;  // consecutive keys of one wave of a tile
+static_assert(kRsThreads == kMaxRadixBins, "one thread per digit in the tile's scan");
+constexpr int32_t kSwapBit = INT32_MIN;      // of a sort value: the match's cameras were exchanged
 
 // Exclusive scan of a 256-thread block's values; returns this thread's
 // exclusive prefix and writes the block total to *total.
@@ -101,162 +117,260 @@ hipError_t device_exclusive_scan(int* data, int64_t n, int* scratch, hipStream_t
   return hipGetLastError();
 }
 
-// Validation and canonical keys: key = i * N + j with i < j.
+// Validation, canonical keys (key = i * N + j with i < j), sort values (input
+// index, top bit set when the cameras are exchanged) and the coordinates in
+// the pair's orientation, one record per match.
 __global__ void k_validate(int64_t n, int N, const int32_t* __restrict__ cam1, const int32_t* __restrict__ cam2,
                            const float* __restrict__ x1, const float* __restrict__ y1,
                            const float* __restrict__ x2, const float* __restrict__ y2,
-                           uint32_t* __restrict__ keys, int32_t* __restrict__ vals, int* __restrict__ err) {
+                           uint32_t* __restrict__ keys, int32_t* __restrict__ vals, float4* __restrict__ rec,
+                           int* __restrict__ err) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n) return;
   const int c1 = cam1[m], c2 = cam2[m];
+  const float a = x1[m], b = y1[m], c = x2[m], d = y2[m];
   int bits = 0;
   if (c1 < 0 || c1 >= N || c2 < 0 || c2 >= N)
     bits |= kErrRange;
   else if (c1 == c2)
     bits |= kErrSameCam;
-  if (!isfinite(x1[m]) || !isfinite(y1[m]) || !isfinite(x2[m]) || !isfinite(y2[m])) bits |= kErrNonFinite;
+  if (!isfinite(a) || !isfinite(b) || !isfinite(c) || !isfinite(d)) bits |= kErrNonFinite;
   if (bits) atomicOr(err, bits);
+  // ids out of range are clamped: the call fails once the error bits are read
   const uint32_t i = (uint32_t)min(max(min(c1, c2), 0), N - 1);
   const uint32_t j = (uint32_t)min(max(max(c1, c2), 0), N - 1);
+  const bool s = c1 > c2;
   keys[m] = i * (uint32_t)N + j;
-  vals[m] = (int32_t)m;
+  vals[m] = (int32_t)m | (s ? kSwapBit : 0);
+  rec[m] = s ? make_float4(c, d, a, b) : make_float4(a, b, c, d);
 }
 
+// Digit counts of every tile, digit-major: hist[digit * n_tiles + tile].
 __global__ __launch_bounds__(kRsThreads) void k_radix_hist(const uint32_t* __restrict__ keys, int64_t n,
-                                                           int shift, int n_tiles, int* __restrict__ hist) {
-  __shared__ int h[kRadixBins];
-  if (threadIdx.x < kRadixBins) h[threadIdx.x] = 0;
+                                                           int shift, int bits, int n_tiles, int* __restrict__ hist) {
+  __shared__ int h[kMaxRadixBins];
+  const int bins = 1 << bits, tid = threadIdx.x;
+  h[tid] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kRsTile + (int64_t)threadIdx.x * kRsPer;
+  const int64_t base = (int64_t)blockIdx.x * kRsTile + tid;
+  uint32_t key[kRsPer];
+#pragma unroll
+  for (int k = 0; k < kRsPer; ++k) key[k] = keys[min(base + k * kRsThreads, n - 1)];  // all in flight together
 #pragma unroll
   for (int k = 0; k < kRsPer; ++k)
-    if (base + k < n) atomicAdd(&h[(keys[base + k] >> shift) & (kRadixBins - 1)], 1);
+    if (base + k * kRsThreads < n) atomicAdd(&h[(key[k] >> shift) & (bins - 1)], 1);
   __syncthreads();
-  if (threadIdx.x < kRadixBins) hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
+  if (tid < bins) hist[(int64_t)tid * n_tiles + blockIdx.x] = h[tid];
 }
 
-// Stable scatter of one radix pass.  Within a tile, thread t owns the kRsPer
-// consecutive keys starting at t*kRsPer; ranks follow (thread, position), so
-// equal digits keep their input order.
+// Stable scatter of one radix pass.  Wave w of a tile owns its kRsWaveTile
+// consecutive keys from w * kRsWaveTile and takes them 64 at a time in input
+// order: the lanes holding the same digit find each other with one ballot
+// per digit bit, a key's rank is the number of such lanes below it plus the
+// wave's count of that digit so far.  The tile is then laid out by digit in
+// LDS and written from there, consecutive lanes to consecutive places of a
+// digit's run.
 __global__ __launch_bounds__(kRsThreads) void k_radix_scatter(const uint32_t* __restrict__ kin,
                                                               const int32_t* __restrict__ vin,
                                                               uint32_t* __restrict__ kout,
                                                               int32_t* __restrict__ vout, int64_t n, int shift,
-                                                              int n_tiles, const int* __restrict__ offs) {
-  __shared__ int s_cnt[kRadixBins * kRsThreads];  // digit-major [d][t]
-  __shared__ int s_w[kRsThreads / 64];
-  const int tid = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * kRsTile + (int64_t)tid * kRsPer;
+                                                              int bits, int n_tiles, const int* __restrict__ offs) {
+  __shared__ uint32_t s_key[kRsTile];
+  __shared__ int32_t s_val[kRsTile];
+  __shared__ int s_cnt[kRsWaves][kMaxRadixBins];
+  __shared__ int s_off[kMaxRadixBins];  // global place of a digit's run minus its place in the tile
+  __shared__ int s_w[kRsWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint32_t dmask = (1u << bits) - 1u;
+  const int64_t tile0 = (int64_t)blockIdx.x * kRsTile;
+  const int64_t base = tile0 + wid * kRsWaveTile + lane;
   uint32_t key[kRsPer];
   int32_t val[kRsPer];
-  int dg[kRsPer];
 #pragma unroll
-  for (int k = 0; k < kRsPer; ++k) {
-    const bool ok = base + k < n;
-    key[k] = ok ? kin[base + k] : 0u;
-    val[k] = ok ? vin[base + k] : 0;
-    dg[k] = ok ? (int)((key[k] >> shift) & (kRadixBins - 1)) : -1;
+  for (int r = 0; r < kRsPer; ++r) {
+    const bool ok = base + r * kWave < n;
+    const int64_t p = ok ? base + r * kWave : n - 1;  // n >= 1; the last key's copies are not used
+    key[r] = kin[p];
+    val[r] = vin[p];
   }
+  for (int d = tid; d < kRsWaves * kMaxRadixBins; d += kRsThreads) (&s_cnt[0][0])[d] = 0;
+  __syncthreads();
+  const uint64_t below = (1ull << lane) - 1ull;
+  int rank[kRsPer];
 #pragma unroll
-  for (int d = 0; d < kRadixBins; ++d) {
-    int c = 0;
-#pragma unroll
-    for (int k = 0; k < kRsPer; ++k) c += (dg[k] == d);
-    s_cnt[d * kRsThreads + tid] = c;
+  for (int r = 0; r < kRsPer; ++r) {
+    const bool ok = base + r * kWave < n;
+    const uint32_t d = (key[r] >> shift) & dmask;
+    uint64_t peers = __ballot(ok);
+    for (int b = 0; b < bits; ++b) {
+      const bool bit = (d >> b) & 1u;
+      const uint64_t m = __ballot(bit);
+      peers &= bit ? m : ~m;
+    }
+    // every lane reads the wave's count before the digit's first lane
+    // raises it (one wave, LDS operations in order)
+    const int before = __hip_atomic_load(&s_cnt[wid][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    const int mine = __popcll(peers & below);
+    __builtin_amdgcn_wave_barrier();
+    if (ok && mine == 0)
+      __hip_atomic_store(&s_cnt[wid][d], before + __popcll(peers), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __builtin_amdgcn_wave_barrier();
+    rank[r] = before + mine;
   }
   __syncthreads();
-  // exclusive scan of the flattened digit-major array (16 entries per thread)
-  int loc[kRadixBins];
-  int sum = 0;
+  {
+    // per digit: the waves' counts to exclusive prefixes, then the digits'
+    // starts within the tile (digits past the pass's bins count zero)
+    int c[kRsWaves], sum = 0;
 #pragma unroll
-  for (int k = 0; k < kRadixBins; ++k) {
-    loc[k] = s_cnt[tid * kRadixBins + k];
-    sum += loc[k];
-  }
-  int total;
-  int run = block_exclusive_scan(sum, &total, s_w);
+    for (int w = 0; w < kRsWaves; ++w) {
+      c[w] = sum;
+      sum += s_cnt[w][tid];
+    }
+    int total;
+    const int start = block_exclusive_scan(sum, &total, s_w);
 #pragma unroll
-  for (int k = 0; k < kRadixBins; ++k) {
-    const int x = loc[k];
-    loc[k] = run;
-    run += x;
+    for (int w = 0; w < kRsWaves; ++w) s_cnt[w][tid] = start + c[w];
+    s_off[tid] = tid <= (int)dmask ? offs[(int64_t)tid * n_tiles + blockIdx.x] - start : 0;
   }
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kRadixBins; ++k) s_cnt[tid * kRadixBins + k] = loc[k];
+  for (int r = 0; r < kRsPer; ++r) {
+    if (base + r * kWave >= n) continue;
+    const int q = s_cnt[wid][(key[r] >> shift) & dmask] + rank[r];
+    s_key[q] = key[r];
+    s_val[q] = val[r];
+  }
   __syncthreads();
+  const int cnt_tile = (int)min((int64_t)kRsTile, n - tile0);
+  for (int q = tid; q < cnt_tile; q += kRsThreads) {
+    const uint32_t k = s_key[q];
+    const int64_t dst = (int64_t)s_off[(k >> shift) & dmask] + q;
+    kout[dst] = k;
+    vout[dst] = s_val[q];
+  }
+}
+
+// The first position of every pair's run ("head") in a wave's kRsWaveTile
+// sorted keys, 64 at a time: bit l of heads[r] for position base + 64 r + l.
+// Returns how many there are.
+__device__ __forceinline__ int wave_heads(const uint32_t* __restrict__ sk, int64_t base, int64_t n, int lane,
+                                          uint32_t (&key)[kRsPer], uint64_t (&heads)[kRsPer]) {
+  int c = 0;
 #pragma unroll
-  for (int k = 0; k < kRsPer; ++k) {
-    if (dg[k] < 0) continue;
-    const int d = dg[k];
-    int r = 0;
+  for (int r = 0; r < kRsPer; ++r) {
+    const int64_t p = base + r * kWave + lane;
+    key[r] = sk[min(p, n - 1)];  // n >= 1
+    const uint32_t prev = sk[max(min(p, n) - 1, (int64_t)0)];
+    heads[r] = __ballot(p < n && (p == 0 || key[r] != prev));
+    c += __popcll(heads[r]);
+  }
+  return c;
+}
+
+// Heads before this wave's keys: the tile's (exclusive scan over the tiles)
+// plus the tile's waves below.
+__device__ __forceinline__ int heads_before(int mine, int tile_base, int wid, int lane, int* s_w) {
+  if (lane == 0) s_w[wid] = mine;
+  __syncthreads();
+  int b = tile_base;
 #pragma unroll
-    for (int q = 0; q < kRsPer; ++q) r += (q < k) && (dg[q] == d);
-    const int local = s_cnt[d * kRsThreads + tid] - s_cnt[d * kRsThreads];
-    const int64_t dst = (int64_t)offs[(int64_t)d * n_tiles + blockIdx.x] + local + r;
-    kout[dst] = key[k];
-    vout[dst] = val[k];
+  for (int w = 0; w < kRsWaves; ++w) b += w < wid ? s_w[w] : 0;
+  return b;
+}
+
+__global__ __launch_bounds__(kRsThreads) void k_head_count(const uint32_t* __restrict__ sk, int64_t n,
+                                                           int* __restrict__ tile_heads) {
+  __shared__ int s_w[kRsWaves];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  uint32_t key[kRsPer];
+  uint64_t heads[kRsPer];
+  const int c = wave_heads(sk, (int64_t)blockIdx.x * kRsTile + wid * kRsWaveTile, n, lane, key, heads);
+  if (lane == 0) s_w[wid] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int t = 0;
+    for (int w = 0; w < kRsWaves; ++w) t += s_w[w];
+    tile_heads[blockIdx.x] = t;
   }
 }
 
-__global__ void k_head_flags(const uint32_t* __restrict__ sk, int64_t n, int* __restrict__ flag) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < n) flag[p] = (p == 0 || sk[p] != sk[p - 1]) ? 1 : 0;
+// Pair table: key and first sorted position of every run, in order.
+__global__ __launch_bounds__(kRsThreads) void k_heads(const uint32_t* __restrict__ sk, int64_t n,
+                                                      const int* __restrict__ tile_base,
+                                                      uint32_t* __restrict__ pair_key,
+                                                      int32_t* __restrict__ seg_start, int* __restrict__ n_pairs) {
+  __shared__ int s_w[kRsWaves];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kRsTile + wid * kRsWaveTile;
+  uint32_t key[kRsPer];
+  uint64_t heads[kRsPer];
+  const int c = wave_heads(sk, base, n, lane, key, heads);
+  int id = heads_before(c, tile_base[blockIdx.x], wid, lane, s_w);
+  if (blockIdx.x == gridDim.x - 1 && wid == kRsWaves - 1 && lane == 0) *n_pairs = id + c;
+#pragma unroll
+  for (int r = 0; r < kRsPer; ++r) {
+    if ((heads[r] >> lane) & 1ull) {
+      const int k = id + __popcll(heads[r] & ((1ull << lane) - 1ull));
+      pair_key[k] = key[r];
+      seg_start[k] = (int32_t)(base + r * kWave + lane);
+    }
+    id += __popcll(heads[r]);
+  }
 }
 
-__global__ void k_heads(const uint32_t* __restrict__ sk, const int* __restrict__ excl, int64_t n,
-                        uint32_t* __restrict__ pair_key, int32_t* __restrict__ seg_start,
-                        int32_t* __restrict__ pid, int* __restrict__ n_pairs) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const int head = (p == 0 || sk[p] != sk[p - 1]) ? 1 : 0;
-  const int id = excl[p] + head - 1;
-  pid[p] = id;
-  if (head) {
-    pair_key[id] = sk[p];
-    seg_start[id] = (int32_t)p;
+// The layout: position p of pair k goes to slot p + shift[k] (the pair's
+// aligned start minus its first position).
+__global__ __launch_bounds__(kRsThreads) void k_gather(const uint32_t* __restrict__ sk, int64_t n,
+                                                       const int* __restrict__ tile_base,
+                                                       const int32_t* __restrict__ sv,
+                                                       const int32_t* __restrict__ shift,
+                                                       const float4* __restrict__ rec, float* __restrict__ ox1,
+                                                       float* __restrict__ oy1, float* __restrict__ ox2,
+                                                       float* __restrict__ oy2, int32_t* __restrict__ opos,
+                                                       int32_t* __restrict__ perm, uint8_t* __restrict__ swp) {
+  __shared__ int s_w[kRsWaves];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kRsTile + wid * kRsWaveTile;
+  uint32_t key[kRsPer];
+  uint64_t heads[kRsPer];
+  const int c = wave_heads(sk, base, n, lane, key, heads);
+  int id = heads_before(c, tile_base[blockIdx.x], wid, lane, s_w) - 1;
+  const uint64_t upto = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1ull;
+#pragma unroll 4
+  for (int r = 0; r < kRsPer; ++r) {
+    const int64_t p = base + r * kWave + lane;
+    const int k = id + __popcll(heads[r] & upto);
+    id += __popcll(heads[r]);
+    if (p >= n) continue;
+    const int32_t v = sv[p];
+    const int32_t m = v & ~kSwapBit;
+    const float4 q = rec[m];
+    const int64_t dst = p + shift[k];
+    __builtin_nontemporal_store(q.x, ox1 + dst);
+    __builtin_nontemporal_store(q.y, oy1 + dst);
+    __builtin_nontemporal_store(q.z, ox2 + dst);
+    __builtin_nontemporal_store(q.w, oy2 + dst);
+    __builtin_nontemporal_store((int32_t)p, opos + dst);
+    __builtin_nontemporal_store(m, perm + p);
+    __builtin_nontemporal_store((uint8_t)(v < 0 ? 1 : 0), swp + p);
   }
-  if (p == n - 1) *n_pairs = id + 1;
 }
 
-__global__ void k_gather(int64_t n, const int32_t* __restrict__ sv, const int32_t* __restrict__ pid,
-                         const int32_t* __restrict__ seg_start, const int32_t* __restrict__ phys_off,
-                         const float* __restrict__ x1, const float* __restrict__ y1,
-                         const float* __restrict__ x2, const float* __restrict__ y2,
-                         const int32_t* __restrict__ cam1, const int32_t* __restrict__ cam2,
-                         float* __restrict__ ox1, float* __restrict__ oy1, float* __restrict__ ox2,
-                         float* __restrict__ oy2, int32_t* __restrict__ opos, int32_t* __restrict__ perm,
-                         uint8_t* __restrict__ swp) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const int32_t m = sv[p];
-  const int32_t k = pid[p];
-  const int64_t dst = (int64_t)phys_off[k] + (p - seg_start[k]);
-  const bool s = cam1[m] > cam2[m];
-  const float a = x1[m], b = y1[m], c = x2[m], d = y2[m];
-  ox1[dst] = s ? c : a;
-  oy1[dst] = s ? d : b;
-  ox2[dst] = s ? a : c;
-  oy2[dst] = s ? b : d;
-  opos[dst] = (int32_t)p;
-  perm[p] = m;
-  swp[p] = s ? 1 : 0;
+// The alignment padding after every pair's run (fewer than kAlign slots):
+// zero coordinates, position -1.  One thread per (pair, slot).
+__global__ void k_pad(int64_t n_pairs, const int32_t* __restrict__ shift, const int32_t* __restrict__ seg_end,
+                      float* __restrict__ ox1, float* __restrict__ oy1, float* __restrict__ ox2,
+                      float* __restrict__ oy2, int32_t* __restrict__ opos) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t k = t / kAlign;
+  if (k >= n_pairs) return;
+  const int64_t end = (int64_t)seg_end[k] + shift[k];  // slot past the pair's last match
+  const int64_t s = end + t % kAlign;
+  if (s >= (end + kAlign - 1) / kAlign * kAlign) return;
+  ox1[s] = oy1[s] = ox2[s] = oy2[s] = 0.f;
+  opos[s] = -1;
 }
-
-struct Scratch {
-  std::vector<void*> ptrs;
-  ~Scratch() {
-    for (void* p : ptrs) (void)hipFree(p);
-  }
-  template <class T>
-  hipError_t alloc(T** out, size_t count) {
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T));
-    if (e == hipSuccess) ptrs.push_back(p);
-    *out = static_cast<T*>(p);
-    return e;
-  }
-};
 
 #define FEA_TRY(expr)                    \
   do {                                   \
@@ -324,76 +438,84 @@ hipError_t export_sorted(fea_ctx* c, int32_t cam_base, const int64_t* seg_off_de
   return hipGetLastError();
 }
 
+// The filtered layouts' buffers (1 and 2) for `slots` slots each: one block
+// per layout, its four coordinate arrays views into it.
+hipError_t alloc_filtered_layouts(fea_ctx* c, int64_t slots) {
+  const size_t each = (std::max<int64_t>(slots, 1) * sizeof(float) + 255) / 256 * 256;
+  for (int b = 1; b < 3; ++b) {
+    if (!(c->lay_block[b].p && c->lay_block[b].bytes >= 4 * each)) {
+      for (int a = 0; a < 4; ++a) c->lay[b][a] = DBuf();
+      FEA_TRY(alloc_dbuf(c->lay_block[b], 4 * each));
+    }
+    const size_t part = c->lay_block[b].bytes / 4 / 256 * 256;
+    for (int a = 0; a < 4; ++a) {
+      c->lay[b][a].p = c->lay_block[b].as<uint8_t>() + a * part;
+      c->lay[b][a].bytes = part;
+    }
+    FEA_TRY(alloc_dbuf(c->lpos[b], each));
+  }
+  return hipSuccess;
+}
+
 hipError_t segment_matches(fea_ctx* c, const float* x1, const float* y1, const float* x2, const float* y2,
                            const int32_t* cam1, const int32_t* cam2, int* bad_bits) {
   hipStream_t st = c->stream;
   const int64_t M = c->M;
   const int N = c->N;
   *bad_bits = 0;
-  Scratch s;
-  uint32_t *k0, *k1, *pair_key;
-  int32_t *v0, *v1, *pid, *seg_start, *phys32;
-  int *flag, *err, *npairs, *scan_scr;
-  FEA_TRY(s.alloc(&k0, M));
-  FEA_TRY(s.alloc(&k1, M));
-  FEA_TRY(s.alloc(&v0, M));
-  FEA_TRY(s.alloc(&v1, M));
-  FEA_TRY(s.alloc(&err, 2));
-  FEA_TRY(hipMemsetAsync(err, 0, 2 * sizeof(int), st));
-  const unsigned g256 = (unsigned)((M + 255) / 256);
-  if (M > 0) {
-    k_validate<<<g256, 256, 0, st>>>(M, N, cam1, cam2, x1, y1, x2, y2, k0, v0, err);
-    FEA_TRY(hipGetLastError());
-  }
-  int h_err = 0;
-  FEA_TRY(hipMemcpyAsync(&h_err, err, sizeof(int), hipMemcpyDeviceToHost, st));
-  FEA_TRY(hipStreamSynchronize(st));
-  if (h_err) {
-    *bad_bits = h_err;
-    return hipSuccess;
-  }
-  // LSD radix sort of (key, input index) by key
+  // the fewest LSD passes of at most kMaxRadixBits over the keys' bits
   const uint64_t max_key = (uint64_t)N * (uint64_t)N;
   int bits = 1;
   while (bits < 32 && (1ull << bits) < max_key) ++bits;
-  const int passes = (bits + kRadixBits - 1) / kRadixBits;
+  const int passes = (bits + kMaxRadixBits - 1) / kMaxRadixBits;
+  const int digit = (bits + passes - 1) / passes;
   const int64_t n_tiles = (M + kRsTile - 1) / kRsTile;
-  int* hist;
-  const int64_t hist_n = kRadixBins * std::max<int64_t>(n_tiles, 1);
-  FEA_TRY(s.alloc(&hist, hist_n));
-  FEA_TRY(s.alloc(&scan_scr, scan_scratch_ints(std::max<int64_t>(hist_n, M))));
-  uint32_t *kin = k0, *kout = k1;
-  int32_t *vin = v0, *vout = v1;
+  const int64_t hist_n = ((int64_t)1 << digit) * std::max<int64_t>(n_tiles, 1);
+  // the filtered layouts hold the sort meanwhile: records in the first one's
+  // block, keys and values (double-buffered) in the second's, the pair table
+  // in their position arrays.  Pairs of 1,000 matches need M / 64 slots of
+  // padding at most; a layout that turns out larger is allocated again below
+  const int64_t max_pairs = std::min<int64_t>(M, (int64_t)N * (N - 1) / 2);
+  FEA_TRY(alloc_filtered_layouts(c, M + std::min<int64_t>(M / 64, (kAlign - 1) * max_pairs)));
+  float4* rec = c->lay_block[1].as<float4>();
+  uint32_t *kin = c->lay[2][0].as<uint32_t>(), *kout = c->lay[2][1].as<uint32_t>();
+  int32_t *vin = c->lay[2][2].as<int32_t>(), *vout = c->lay[2][3].as<int32_t>();
+  uint32_t* pair_key = c->lpos[1].as<uint32_t>();
+  int32_t* seg_start = c->lpos[2].as<int32_t>();
+  const int64_t scr_n = scan_scratch_ints(std::max<int64_t>(hist_n, n_tiles));
+  FEA_TRY(alloc_dbuf(c->seg_ws, (size_t)(2 + n_tiles + 1 + hist_n + scr_n) * sizeof(int)));
+  int* err = c->seg_ws.as<int>();  // error bits, pair count
+  int *tile_heads = err + 2, *hist = tile_heads + n_tiles + 1, *scan_scr = hist + hist_n;
+  int h_head[2] = {0, 0};
   if (M > 0) {
+    FEA_TRY(hipMemsetAsync(err, 0, 2 * sizeof(int), st));
+    k_validate<<<(unsigned)((M + 255) / 256), 256, 0, st>>>(M, N, cam1, cam2, x1, y1, x2, y2, kin, vin, rec, err);
+    FEA_TRY(hipGetLastError());
     for (int ps = 0; ps < passes; ++ps) {
-      const int shift = ps * kRadixBits;
-      k_radix_hist<<<(unsigned)n_tiles, kRsThreads, 0, st>>>(kin, M, shift, (int)n_tiles, hist);
+      const int shift = ps * digit;
+      k_radix_hist<<<(unsigned)n_tiles, kRsThreads, 0, st>>>(kin, M, shift, digit, (int)n_tiles, hist);
       FEA_TRY(hipGetLastError());
       FEA_TRY(device_exclusive_scan(hist, hist_n, scan_scr, st));
-      k_radix_scatter<<<(unsigned)n_tiles, kRsThreads, 0, st>>>(kin, vin, kout, vout, M, shift, (int)n_tiles,
+      k_radix_scatter<<<(unsigned)n_tiles, kRsThreads, 0, st>>>(kin, vin, kout, vout, M, shift, digit, (int)n_tiles,
                                                                 hist);
       FEA_TRY(hipGetLastError());
       std::swap(kin, kout);
       std::swap(vin, vout);
     }
-  }
-  // pair runs
-  FEA_TRY(s.alloc(&flag, M));
-  FEA_TRY(s.alloc(&pid, M));
-  FEA_TRY(s.alloc(&pair_key, M));
-  FEA_TRY(s.alloc(&seg_start, M));
-  npairs = err + 1;
-  int h_np = 0;
-  if (M > 0) {
-    k_head_flags<<<g256, 256, 0, st>>>(kin, M, flag);
+    // pair runs
+    k_head_count<<<(unsigned)n_tiles, kRsThreads, 0, st>>>(kin, M, tile_heads);
     FEA_TRY(hipGetLastError());
-    FEA_TRY(device_exclusive_scan(flag, M, scan_scr, st));
-    k_heads<<<g256, 256, 0, st>>>(kin, flag, M, pair_key, seg_start, pid, npairs);
+    FEA_TRY(device_exclusive_scan(tile_heads, n_tiles, scan_scr, st));
+    k_heads<<<(unsigned)n_tiles, kRsThreads, 0, st>>>(kin, M, tile_heads, pair_key, seg_start, err + 1);
     FEA_TRY(hipGetLastError());
-    FEA_TRY(hipMemcpyAsync(&h_np, npairs, sizeof(int), hipMemcpyDeviceToHost, st));
+    FEA_TRY(hipMemcpyAsync(h_head, err, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
     FEA_TRY(hipStreamSynchronize(st));
+    if (h_head[0]) {
+      *bad_bits = h_head[0];
+      return hipSuccess;
+    }
   }
-  const int64_t P = h_np;
+  const int64_t P = h_head[1];
   std::vector<uint32_t> h_key(P);
   std::vector<int32_t> h_start(P);
   if (P > 0) {
@@ -407,40 +529,45 @@ hipError_t segment_matches(fea_ctx* c, const float* x1, const float* y1, const f
   c->seg_off.resize(P + 1);
   c->phys_off.resize(P);
   c->cur_len.resize(P);
-  std::vector<int32_t> h_phys(P);
+  std::vector<int32_t> h_shift(2 * P);  // per pair: slot minus position, then the pairs' ends
   int64_t off = 0;
   for (int64_t k = 0; k < P; ++k) {
     c->pair_i[k] = (int32_t)(h_key[k] / (uint32_t)N);
     c->pair_j[k] = (int32_t)(h_key[k] % (uint32_t)N);
     c->seg_off[k] = h_start[k];
-    const int64_t len = ((k + 1 < P) ? (int64_t)h_start[k + 1] : M) - h_start[k];
+    const int64_t end = (k + 1 < P) ? (int64_t)h_start[k + 1] : M, len = end - h_start[k];
     c->cur_len[k] = len;
     c->phys_off[k] = off;
-    h_phys[k] = (int32_t)off;
+    h_shift[k] = (int32_t)(off - h_start[k]);
+    h_shift[P + k] = (int32_t)end;
     off += (len + kAlign - 1) / kAlign * kAlign;
   }
   c->seg_off[P] = M;
   c->layout_len = off;
   c->cur = 0;
+  if (off >= (int64_t)1 << 31) return hipSuccess;  // refused by the caller
   // the full device layout (buffer 0; the filtered rounds use buffers 1, 2)
   const size_t cap = (size_t)std::max<int64_t>(off, 1);
   for (int a = 0; a < 4; ++a) FEA_TRY(alloc_dbuf(c->lay[0][a], cap * sizeof(float)));
   FEA_TRY(alloc_dbuf(c->lpos[0], cap * sizeof(int32_t)));
   FEA_TRY(alloc_dbuf(c->perm, std::max<int64_t>(M, 1) * sizeof(int32_t)));
   FEA_TRY(alloc_dbuf(c->swp, std::max<int64_t>(M, 1)));
-  for (int a = 0; a < 4; ++a) FEA_TRY(hipMemsetAsync(c->lay[0][a].p, 0, cap * sizeof(float), st));
-  FEA_TRY(hipMemsetAsync(c->lpos[0].p, 0xFF, cap * sizeof(int32_t), st));
-  if (M > 0) {
-    FEA_TRY(s.alloc(&phys32, P));
-    FEA_TRY(hipMemcpyAsync(phys32, h_phys.data(), P * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    k_gather<<<g256, 256, 0, st>>>(M, vin, pid, seg_start, phys32, x1, y1, x2, y2, cam1, cam2,
-                                   c->lay[0][0].as<float>(), c->lay[0][1].as<float>(), c->lay[0][2].as<float>(),
-                                   c->lay[0][3].as<float>(), c->lpos[0].as<int32_t>(), c->perm.as<int32_t>(),
-                                   c->swp.as<uint8_t>());
+  if (P > 0) {
+    float *o1 = c->lay[0][0].as<float>(), *o2 = c->lay[0][1].as<float>(), *o3 = c->lay[0][2].as<float>(),
+          *o4 = c->lay[0][3].as<float>();
+    int32_t* opos = c->lpos[0].as<int32_t>();
+    // the shifts and ends take the pair table's place (its copy is on the host)
+    FEA_TRY(hipMemcpyAsync(c->lpos[1].p, h_shift.data(), P * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    FEA_TRY(hipMemcpyAsync(c->lpos[2].p, h_shift.data() + P, P * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    const int32_t *shift = c->lpos[1].as<int32_t>(), *ends = c->lpos[2].as<int32_t>();
+    k_gather<<<(unsigned)n_tiles, kRsThreads, 0, st>>>(kin, M, tile_heads, vin, shift, rec, o1, o2, o3, o4, opos,
+                                                       c->perm.as<int32_t>(), c->swp.as<uint8_t>());
+    FEA_TRY(hipGetLastError());
+    k_pad<<<(unsigned)((P * kAlign + 255) / 256), 256, 0, st>>>(P, shift, ends, o1, o2, o3, o4, opos);
     FEA_TRY(hipGetLastError());
   }
   FEA_TRY(hipStreamSynchronize(st));
-  return hipSuccess;
+  return alloc_filtered_layouts(c, off);
 }
 
 }  // namespace fea
