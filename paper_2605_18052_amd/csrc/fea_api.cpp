@@ -2526,9 +2526,12 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
   for (int64_t n = 0; n < P; ++n) {
     const int64_t cnt = c->seg_off[n + 1] - c->seg_off[n];
     pio[n] = (int32_t)items.size();
-    for (int64_t s = 0; s < cnt; s += fea::kRtItem) {
+    // equal runs of at most kRtItem, whole blocks of 32 matches but the last
+    const int64_t runs = (cnt + fea::kRtItem - 1) / fea::kRtItem;
+    const int64_t len = runs > 0 ? ((cnt + runs - 1) / runs + 31) / 32 * 32 : 0;
+    for (int64_t s = 0; s < cnt; s += len) {
       if (off + s > INT32_MAX) return fail(c, FEA_EINVAL, "layout too large for the candidate search");
-      items.push_back(make_int4((int)n, (int)(off + s), (int)std::min<int64_t>(fea::kRtItem, cnt - s), 0));
+      items.push_back(make_int4((int)n, (int)(off + s), (int)std::min<int64_t>(len, cnt - s), 0));
     }
     off += (cnt + fea::kAlign - 1) / fea::kAlign * fea::kAlign;
   }
@@ -2543,7 +2546,7 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
   DeviceGuard g(c->device);
   CallScratch sc(c->stream);
   double *dR, *df, *rowd, *dt, *dsb;
-  float *dcand, *rowf, *part, *dscores = nullptr;
+  float *dcand, *rowf, *part, *iabs, *dscores = nullptr;
   int4* ditems;
   int32_t *dpio, *dbest, *dvote;
   HIP_OR_FAIL(c, sc.put(dR, R, (size_t)9 * N));
@@ -2554,6 +2557,7 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
   HIP_OR_FAIL(c, sc.alloc(rowf, (size_t)fea::kRtRow * P));
   HIP_OR_FAIL(c, sc.alloc(rowd, (size_t)fea::kRtRow * P));
   HIP_OR_FAIL(c, sc.alloc(part, (size_t)n_items * kp));
+  HIP_OR_FAIL(c, sc.alloc(iabs, (size_t)n_items));
   HIP_OR_FAIL(c, sc.alloc(dbest, (size_t)P));
   HIP_OR_FAIL(c, sc.alloc(dvote, (size_t)P));
   HIP_OR_FAIL(c, sc.alloc(dt, (size_t)3 * P));
@@ -2568,11 +2572,11 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
     HIP_OR_FAIL(c, hipEventCreate(&ev[0]));
     HIP_OR_FAIL(c, hipEventCreate(&ev[1]));
   }
-  hipError_t e = fea::launch_rt_score(c->stream, n_items, groups, ditems, rowf, x1, y1, x2, y2, dcand, kp, tau,
-                                      part, ev[0], ev[1]);
+  hipError_t e = fea::launch_rt_score(c->stream, n_items, groups, ditems, rowf, x1, y1, x2, y2, dcand, n_cand, kp,
+                                      tau, part, iabs, ev[0], ev[1]);
   if (e == hipSuccess)
-    e = fea::launch_rt_select(c->stream, P, n_cand, kp, tau, dpio, ditems, part, dcand, rowd, x1, y1, x2, y2,
-                              dscores, dbest, dvote, dt, dsb);
+    e = fea::launch_rt_select(c->stream, P, n_cand, kp, tau, dpio, ditems, part, iabs, dcand, rowf, rowd, x1, y1, x2,
+                              y2, dscores, dbest, dvote, dt, dsb);
   if (e == hipSuccess) e = fetch(c->stream, t_rel, dt, (size_t)3 * P);
   if (e == hipSuccess) e = fetch(c->stream, best, dbest, (size_t)P);
   if (e == hipSuccess) e = fetch(c->stream, vote, dvote, (size_t)P);

@@ -6,9 +6,11 @@
 // scalar triple product eps(u) = u . n with n = (R_ij x~1) x x~2, so a pair
 // with M matches and K candidates is the product of an M x 3 and a 3 x K
 // matrix followed by |.| and a sum over M: a dense contraction of depth 3.
-// It runs on the fp32 matrix cores (v_mfma_f32_16x16x4f32, the fourth depth
-// slot zero), |D| accumulated per lane; n is computed once per match into LDS.
-// A direction and its opposite score the same; the sign comes from a
+// It runs on the matrix cores with both factors split into bf16 parts that
+// carry fp32's 24 bits between them, |D| accumulated per lane in fp32; n is
+// computed once per match into LDS.  The candidates that come out lowest are
+// scored once more with fp32 products (v_mfma_f32_16x16x4f32), and the choice
+// is made among those.  A direction and its opposite score the same; the sign comes from a
 // cheirality vote (both triangulated depths positive) over the pair's matches.
 //
 // Camera centres.  The L1 direction loss of
@@ -32,10 +34,15 @@
 namespace fea {
 namespace {
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRtThreads = 256;
-constexpr int kRtLds = kRtItem + 16;              // LDS row stride (floats): rows land 16 banks apart
+constexpr int kRtLds = kRtItem + 32;              // LDS row stride (floats): a block past the last is readable
 constexpr int kTaThreads = 256;
 
 // ---- relative translations ---------------------------------------------------
@@ -70,98 +77,235 @@ __global__ void k_rt_pairs(int64_t n_pairs, const int32_t* __restrict__ pair_i, 
   rowf[kRtRow * n + 10] = (float)(1.0 / row[10]);
 }
 
-// Scores of kRtGroup candidates over one work item.  MFMA 16x16x4 (fp32):
-// lane l supplies A[l%16][l/16] = component l/16 of match l%16 of the block
-// and B[l/16][l%16] = component l/16 of candidate l%16; it receives D[4(l/16)+r][l%16]
-// for r = 0..3, i.e. four matches of candidate l%16.  Component 3 is zero.
-// With CAP every product enters as min(|d|, tau) (one v_med3_f32 clamp each,
-// the absolute value folded into the adds), else as |d| (folded into the adds).
+// A match's n = (R_ij x~1) x x~2 in fp32, x~2 = (b0, b1, 1).  The roundings
+// are spelled out: the scoring and the second scoring of the lowest
+// candidates form the same bits.
+struct RtPair {
+  float R[9], ifi, ifj, cxi, cyi, cxj, cyj;
+  __device__ __forceinline__ explicit RtPair(const float* __restrict__ row) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) R[k] = row[k];
+    ifi = row[9];
+    ifj = row[10];
+    cxi = row[11];
+    cyi = row[12];
+    cxj = row[13];
+    cyj = row[14];
+  }
+  __device__ __forceinline__ void normal(float x1, float y1, float x2, float y2, float (&n)[3]) const {
+    const float a0 = (x1 - cxi) * ifi, a1 = (y1 - cyi) * ifi;
+    const float b0 = (x2 - cxj) * ifj, b1 = (y2 - cyj) * ifj;
+    const float r0 = fmaf(R[0], a0, R[1] * a1) + R[2];
+    const float r1 = fmaf(R[3], a0, R[4] * a1) + R[5];
+    const float r2 = fmaf(R[6], a0, R[7] * a1) + R[8];
+    n[0] = fmaf(-b1, r2, r1);
+    n[1] = fmaf(b0, r2, -r0);
+    n[2] = fmaf(b1, r0, -(b0 * r1));
+  }
+};
+
+// x rounded to bf16 in both halves of a register.
+__device__ __forceinline__ unsigned bf16_twice(float x) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){x, x}, bf16x2));
+}
+
+// fp32 x = h + m + l in bf16 parts (8 bits of the significand each).  The dot
+// product of a match's (l l h m h m h m) and a candidate's (h m l l m m h h)
+// is the product of the two but for l l, 2^-32 of it.
+struct Bf16Parts {
+  unsigned hm, ll, hh, mm;  // pairs of parts, the first in the low half
+  __device__ __forceinline__ explicit Bf16Parts(float x) {
+    hh = bf16_twice(x);
+    const float r1 = x - __uint_as_float(hh & 0xffff0000u);
+    mm = bf16_twice(r1);
+    ll = bf16_twice(r1 - __uint_as_float(mm & 0xffff0000u));
+    hm = (hh & 0xffffu) | (mm & 0xffff0000u);
+  }
+  __device__ __forceinline__ bf16x8 candidate() const {
+    return __builtin_bit_cast(bf16x8, (u32x4){hm, ll, mm, hh});
+  }
+};
+__device__ __forceinline__ bf16x8 match_operand(unsigned hm, unsigned ll) {
+  return __builtin_bit_cast(bf16x8, (u32x4){ll, hm, hm, hm});
+}
+
+// Sums of kRtGroup candidates over one work item.  MFMA 32x32x16 (bf16): lane
+// l supplies 8 contraction slots of match l%32 (A) and of candidate l%32 (B),
+// the parts of one component: component l/32 in the first product, 2 (lanes
+// 0-31; the others zero) in the second, which adds to it; the lane receives
+// candidate l%32 at 16 of the 32 matches.  With CAP every product enters as
+// min(|d|, tau) (one v_med3_f32 clamp each, the absolute value folded into
+// the adds), else as |d| (folded into the adds).
+//
+// Bound by the vector unit: 8 instructions (32 cycles) per 256 products with
+// the cap, beside 16 cycles of matrix unit; issue of the two overlaps only in
+// part.  fp32 products (16x16x4, 32 cycles per 256, a quarter of its depth
+// unused) held the vector unit up longer: the inner loop alone took 62.9
+// cycles per 256 products, against 41.0 (capped) and 33.1 (plain) in this
+// form; with 16x16x32 products 46.6, with 256 candidates per wave 86
+// (registers).  30M matches, 2,048 candidates, cap 8 px: 5,971 -> 4,406 us.
+// The sums' error against fp64 is not above the fp32 products' (relative,
+// norm over all scores: 7.1e-8 for 1.8e-7 capped at 8 px, 4.8e-8 for 5.2e-8
+// uncapped).
 template <bool CAP>
 __global__ __launch_bounds__(kRtThreads) void k_rt_score(const int4* __restrict__ items, int n_groups,
                                                          const float* __restrict__ rowf,
                                                          const float* __restrict__ x1, const float* __restrict__ y1,
                                                          const float* __restrict__ x2, const float* __restrict__ y2,
-                                                         const float* __restrict__ cand, int kp, float tau,
-                                                         float* __restrict__ partial) {
-  __shared__ float sn[3][kRtLds];
+                                                         const float* __restrict__ cand, int n_cand, int kp, float tau,
+                                                         float* __restrict__ partial, float* __restrict__ item_abs) {
+  __shared__ unsigned s_hm[3][kRtLds], s_ll[3][kRtLds];  // n's parts
+  __shared__ float s_abs[kRtThreads / 64];
   const int it = blockIdx.x / n_groups;
   const int grp = blockIdx.x - it * n_groups;
   const int4 rec = items[it];  // {pair, layout start, count, -}
-  const float* row = rowf + (int64_t)kRtRow * rec.x;
-  float Rm[9];
-  for (int k = 0; k < 9; ++k) Rm[k] = row[k];
-  const float ifi = row[9], ifj = row[10], cxi = row[11], cyi = row[12], cxj = row[13], cyj = row[14];
   const int cnt = rec.z;
-  const int nblk = (cnt + 15) >> 4;
-  for (int m = threadIdx.x; m < (nblk << 4); m += kRtThreads) {
-    float n0 = 0.f, n1 = 0.f, n2 = 0.f;
-    if (m < cnt) {
-      const int64_t s = (int64_t)rec.y + m;
-      const float a0 = (x1[s] - cxi) * ifi, a1 = (y1[s] - cyi) * ifi;
-      const float b0 = (x2[s] - cxj) * ifj, b1 = (y2[s] - cyj) * ifj;
-      const float r0 = Rm[0] * a0 + Rm[1] * a1 + Rm[2];
-      const float r1 = Rm[3] * a0 + Rm[4] * a1 + Rm[5];
-      const float r2 = Rm[6] * a0 + Rm[7] * a1 + Rm[8];
-      // n = (R_ij x~1) x x~2 with x~2 = (b0, b1, 1)
-      n0 = r1 - r2 * b1;
-      n1 = r2 * b0 - r0;
-      n2 = r0 * b1 - r1 * b0;
+  const int nblk = (cnt + 31) >> 5;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  {
+    const RtPair pr(rowf + (int64_t)kRtRow * rec.x);
+    float sum = 0.f;
+    for (int m = threadIdx.x; m < (nblk << 5); m += kRtThreads) {
+      float n[3] = {0.f, 0.f, 0.f};
+      if (m < cnt) {
+        const int64_t s = (int64_t)rec.y + m;
+        pr.normal(x1[s], y1[s], x2[s], y2[s], n);
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const Bf16Parts p(n[k]);
+        s_hm[k][m] = p.hm;
+        s_ll[k][m] = p.ll;
+      }
+      sum += (__builtin_fabsf(n[0]) + __builtin_fabsf(n[1])) + __builtin_fabsf(n[2]);
     }
-    sn[0][m] = n0;
-    sn[1][m] = n1;
-    sn[2][m] = n2;
+    if (grp == 0) {
+      sum = wave_sum_f32(sum);
+      if (lane == 0) s_abs[wave] = sum;
+    }
   }
   __syncthreads();
+  if (grp == 0 && threadIdx.x == 0) item_abs[it] = (s_abs[0] + s_abs[1]) + (s_abs[2] + s_abs[3]);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int kq = lane >> 4, col = lane & 15;
-  const int cbase = grp * kRtGroup + wave * (kRtBlocks * 16);
-  float bop[kRtBlocks];
+  const int hf = lane >> 5, col = lane & 31;
+  const int cbase = grp * kRtGroup + wave * (kRtBlocks * 32);
+  if (cbase >= n_cand) return;  // the whole wave: nothing but padding
+  bf16x8 b01[kRtBlocks], b2[kRtBlocks];
 #pragma unroll
-  for (int q = 0; q < kRtBlocks; ++q) bop[q] = kq < 3 ? cand[(int64_t)kq * kp + cbase + 16 * q + col] : 0.f;
-  float accf[kRtBlocks], acc2[kRtBlocks];
+  for (int q = 0; q < kRtBlocks; ++q) {
+    const int k = cbase + 32 * q + col;
+    b01[q] = Bf16Parts(cand[(int64_t)hf * kp + k]).candidate();
+    b2[q] = Bf16Parts(hf ? 0.f : cand[(int64_t)2 * kp + k]).candidate();
+  }
+  float accf[kRtBlocks];
+  double acc2[kRtBlocks];
 #pragma unroll
   for (int q = 0; q < kRtBlocks; ++q) {
     accf[q] = 0.f;
-    acc2[q] = 0.f;
+    acc2[q] = 0.0;
   }
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   const float ntau = -tau;
-  // the row of the next block is read while this one's products run (the
-  // read past the last block stays inside the LDS row: nblk * 16 < kRtLds)
-  const float* srow = sn[kq < 3 ? kq : 0];
-  float a_next = srow[col];
+  // the rows of the next block are read while this one's products run (the
+  // read past the last block stays inside the LDS row); in the second product
+  // lanes 32-63 meet candidate parts of zero
+  unsigned hm01 = s_hm[hf][col], ll01 = s_ll[hf][col], hm2 = s_hm[2][col], ll2 = s_ll[2][col];
   for (int mb = 0; mb < nblk; ++mb) {
-    const float a = kq < 3 ? a_next : 0.f;
-    a_next = srow[((mb + 1) << 4) + col];
+    const bf16x8 a01 = match_operand(hm01, ll01), a2 = match_operand(hm2, ll2);
+    const int nx = ((mb + 1) << 5) + col;
+    hm01 = s_hm[hf][nx];
+    ll01 = s_ll[hf][nx];
+    hm2 = s_hm[2][nx];
+    ll2 = s_ll[2][nx];
 #pragma unroll
     for (int q = 0; q < kRtBlocks; ++q) {
-      const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bop[q], zero, 0, 0, 0);
-      if constexpr (CAP) {
-        // |clamp(e, -tau, tau)| = min(|e|, tau): one v_med3 per product, the
-        // absolute value rides on the add as a source modifier (fminf would
-        // add a canonicalising max before every min)
-        const float c0 = __builtin_amdgcn_fmed3f(d[0], ntau, tau), c1 = __builtin_amdgcn_fmed3f(d[1], ntau, tau);
-        const float c2 = __builtin_amdgcn_fmed3f(d[2], ntau, tau), c3 = __builtin_amdgcn_fmed3f(d[3], ntau, tau);
-        accf[q] += (__builtin_fabsf(c0) + __builtin_fabsf(c1)) + (__builtin_fabsf(c2) + __builtin_fabsf(c3));
-      } else
-        accf[q] += (__builtin_fabsf(d[0]) + __builtin_fabsf(d[1])) + (__builtin_fabsf(d[2]) + __builtin_fabsf(d[3]));
+      f32x16 d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a01, b01[q], (f32x16){}, 0, 0, 0);
+      d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, b2[q], d, 0, 0, 0);
+      float c[16];
+      // |clamp(e, -tau, tau)| = min(|e|, tau): one v_med3 per product, the
+      // absolute value rides on the add as a source modifier (fminf would
+      // add a canonicalising max before every min)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) c[r] = __builtin_fabsf(CAP ? __builtin_amdgcn_fmed3f(d[r], ntau, tau) : d[r]);
+#pragma unroll
+      for (int w = 8; w >= 1; w >>= 1)
+#pragma unroll
+        for (int r = 0; r < w; ++r) c[r] = c[2 * r] + c[2 * r + 1];
+      accf[q] += c[0];
     }
-    if ((mb & 31) == 31) {  // lane sums of at most 128 terms, then at most 4 of those
+    if ((mb & 7) == 7) {  // lane sums of at most 128 terms in fp32, those in fp64
 #pragma unroll
       for (int q = 0; q < kRtBlocks; ++q) {
-        acc2[q] += accf[q];
+        acc2[q] += (double)accf[q];
         accf[q] = 0.f;
       }
     }
   }
 #pragma unroll
   for (int q = 0; q < kRtBlocks; ++q) {
-    double s = (double)acc2[q] + (double)accf[q];
-    s += __shfl_xor(s, 16);
+    double s = acc2[q] + (double)accf[q];
     s += __shfl_xor(s, 32);
-    if (kq == 0) partial[(int64_t)it * kp + cbase + 16 * q + col] = (float)s;
+    if (hf == 0) partial[(int64_t)it * kp + cbase + 32 * q + col] = (float)s;
   }
+}
+
+// Part of a candidate's (capped) sum over a run of matches with fp32
+// products, one candidate per column, by one wave: kRtSeg blocks of 16
+// matches from block mb0 on.  MFMA 16x16x4: lane l supplies component l/16
+// of match l%16 and u = component l/16 of the column's candidate (component 3
+// zero) and receives candidate l%16 at four matches.  The order of the sum is
+// fixed, so it does not depend on the column or the wave.
+constexpr int kRtSeg = 32;     // 128 terms per lane
+constexpr int kRtRun = 2048;   // matches whose sum is rounded to fp32: kRtWaves segments
+constexpr int kRtWaves = kRtThreads / 64;
+static_assert(kRtRun == kRtWaves * kRtSeg * 16, "one segment of a run per wave");
+__device__ float rt_segment_sum(const RtPair& pr, int64_t start, int cnt, int mb0, float u, bool cap, float tau,
+                                int lane, float (*sn)[64], const float* __restrict__ x1,
+                                const float* __restrict__ y1, const float* __restrict__ x2,
+                                const float* __restrict__ y2) {
+  const int kq = lane >> 4, col = lane & 15;
+  const int nblk = min((cnt + 15) >> 4, mb0 + kRtSeg);
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const float ntau = -tau;
+  float acc = 0.f;
+  // four blocks at a time: a match per lane, its n through the wave's rows
+  // sn [4][64] in LDS (the fourth zero) to the lanes that supply it
+  float q0 = 0.f, q1 = 0.f, q2 = 0.f, q3 = 0.f;
+  auto load = [&](int mb) {
+    const int64_t s = start + min((mb << 4) + lane, cnt - 1);
+    q0 = x1[s];
+    q1 = y1[s];
+    q2 = x2[s];
+    q3 = y2[s];
+  };
+  if (mb0 < nblk) load(mb0);
+  for (int mb = mb0; mb < nblk; mb += 4) {
+    float n[3];
+    pr.normal(q0, q1, q2, q3, n);
+    load(mb + 4);  // the next four blocks' coordinates, in flight meanwhile (clamped to the run)
+    const bool in = (mb << 4) + lane < cnt;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();  // the rows' last reads come before
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sn[k][lane] = in ? n[k] : 0.f;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    float a[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) a[b] = sn[kq][(b << 4) + col];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b], u, zero, 0, 0, 0);
+      if (mb + b >= nblk) break;  // uniform
+      if (cap) {
+        const float c0 = __builtin_amdgcn_fmed3f(d[0], ntau, tau), c1 = __builtin_amdgcn_fmed3f(d[1], ntau, tau);
+        const float c2 = __builtin_amdgcn_fmed3f(d[2], ntau, tau), c3 = __builtin_amdgcn_fmed3f(d[3], ntau, tau);
+        acc += (__builtin_fabsf(c0) + __builtin_fabsf(c1)) + (__builtin_fabsf(c2) + __builtin_fabsf(c3));
+      } else {
+        acc += (__builtin_fabsf(d[0]) + __builtin_fabsf(d[1])) + (__builtin_fabsf(d[2]) + __builtin_fabsf(d[3]));
+      }
+    }
+  }
+  return acc;
 }
 
 // Depth signs of one match for the translation direction u (camera j frame):
@@ -191,13 +335,28 @@ __device__ int cheirality_vote(const double* row, float fx1, float fy1, float fx
 }
 
 // Per pair: mean score of every candidate (sum of the item partials over the
-// pair's match count), the lowest (ties: lower index), then the vote of the
-// matches with |eps| < tau at that direction.
+// pair's match count); the candidates whose mean may be the lowest in fp32
+// arithmetic scored again with fp32 products (rt_segment_sum); of those the
+// lowest (ties: lower index); then the vote of the matches with |eps| < tau
+// at that direction.
+//
+// A product of the split parts is within 70 * 2^-24 |n|_1 of the fp32 one
+// (|u| components at most 1; 24 terms added in fp32 against 3, and l l), the
+// cap brings them no further apart, and the lane sums round by at most 200
+// * 2^-24 of the score between both forms; so a candidate whose mean is more
+// than twice that bound above the lowest mean cannot be the lowest one: of
+// 2,048 a few remain, and the choice and its score are those of fp32
+// products throughout.  Anything not finite leaves every candidate in.
+// 10,600 pairs of 2,800 matches: 213 us with the vote alone, 367 us with the
+// second scoring.
+constexpr int kRtChunk = 1024;  // candidates looked through at a time
 __global__ __launch_bounds__(kRtThreads) void k_rt_select(int k_cand, int kp, double tau,
                                                           const int32_t* __restrict__ pair_item_off,
                                                           const int4* __restrict__ items,
                                                           const float* __restrict__ partial,
+                                                          const float* __restrict__ item_abs,
                                                           const float* __restrict__ cand,
+                                                          const float* __restrict__ rowf,
                                                           const double* __restrict__ rowd,
                                                           const float* __restrict__ x1, const float* __restrict__ y1,
                                                           const float* __restrict__ x2, const float* __restrict__ y2,
@@ -206,33 +365,113 @@ __global__ __launch_bounds__(kRtThreads) void k_rt_select(int k_cand, int kp, do
                                                           double* __restrict__ score_best) {
   __shared__ double sv[kRtThreads];
   __shared__ int si[kRtThreads];
+  __shared__ int s_list[kRtChunk];      // contenders of the chunk
+  __shared__ double s_mean[kRtChunk];   // and their means in fp32 arithmetic
+  __shared__ int s_slot[kRtChunk];      // candidate of the chunk -> its place in the list, -1 when ruled out
+  __shared__ float s_seg[kRtWaves][64];
+  __shared__ float s_rows[kRtWaves][4][64];
+  __shared__ int s_n;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t n = blockIdx.x;
   const int i0 = pair_item_off[n], i1 = pair_item_off[n + 1];
-  int64_t cnt = 0;
-  for (int it = i0; it < i1; ++it) cnt += items[it].z;
-  double bv = 0.0;
-  int bk = -1;
-  for (int k = threadIdx.x; k < k_cand; k += kRtThreads) {
+  const int64_t start = items[i0].y;  // the pair's items are one run of the layout
+  int cnt = 0;
+  double abs1 = 0.0;
+  for (int it = i0; it < i1; ++it) {
+    cnt += items[it].z;
+    abs1 += (double)item_abs[it];
+  }
+  auto mean_of = [&](int k) {
     double s = 0.0;
     for (int it = i0; it < i1; ++it) s += (double)partial[(int64_t)it * kp + k];
-    const double mean = s / (double)cnt;
+    return s / (double)cnt;
+  };
+  double lo = INFINITY;
+  bool odd = false;
+  for (int k = tid; k < k_cand; k += kRtThreads) {
+    const double mean = mean_of(k);
     if (scores) scores[n * k_cand + k] = (float)mean;
-    if (bk < 0 || mean < bv) {
-      bv = mean;
-      bk = k;
-    }
+    if (mean < lo) lo = mean;
+    odd = odd || !isfinite(mean);
   }
-  sv[threadIdx.x] = bv;
-  si[threadIdx.x] = bk;
+  sv[tid] = lo;
   __syncthreads();
   for (int s = kRtThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      const double v2 = sv[threadIdx.x + s];
-      const int k2 = si[threadIdx.x + s];
-      const int k1 = si[threadIdx.x];
-      if (k2 >= 0 && (k1 < 0 || v2 < sv[threadIdx.x] || (v2 == sv[threadIdx.x] && k2 < k1))) {
-        sv[threadIdx.x] = v2;
-        si[threadIdx.x] = k2;
+    if (tid < s && sv[tid + s] < sv[tid]) sv[tid] = sv[tid + s];
+    __syncthreads();
+  }
+  const double low = sv[0];
+  s_rows[wave][3][lane] = 0.f;
+  __syncthreads();
+  const double limit = low + 2.0 * 0x1p-24 * (70.0 * (abs1 / (double)cnt) + 200.0 * low);
+  const bool none = !odd && lo > limit;  // none of this thread's candidates remains
+  const RtPair pr(rowf + (int64_t)kRtRow * n);
+  const bool cap = !isinf(tau);
+  const float tauf = cap ? (float)tau : 0.f;
+  double bv = 0.0;
+  int bk = -1;
+  for (int c0 = 0; c0 < k_cand; c0 += kRtChunk) {
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    const int ce = min(c0 + kRtChunk, k_cand);
+    for (int k = c0 + tid; k < ce; k += kRtThreads) {
+      int slot = -1;
+      if (!none && !(mean_of(k) > limit)) {
+        slot = atomicAdd(&s_n, 1);
+        s_list[slot] = k;
+        s_mean[slot] = 0.0;
+      }
+      s_slot[k - c0] = slot;
+    }
+    __syncthreads();
+    const int nc = s_n;
+    for (int b = 0; b < nc; b += 16) {
+      // 16 contenders at a time over runs of kRtRun matches, a segment per
+      // wave: the full segments' lane sums are added in order, then the
+      // last, shorter one's and the lanes' in fp64
+      const int kq = lane >> 4, mine = b + (lane & 15);
+      const float u = kq < 3 && mine < nc ? cand[(int64_t)kq * kp + s_list[mine]] : 0.f;
+      for (int m0 = 0; m0 < cnt; m0 += kRtRun) {
+        const int rc = min(kRtRun, cnt - m0), nblk = (rc + 15) >> 4;
+        s_seg[wave][lane] =
+            rt_segment_sum(pr, start + m0, rc, wave * kRtSeg, u, cap, tauf, lane, s_rows[wave], x1, y1, x2, y2);
+        __syncthreads();
+        if (wave == 0) {
+          float acc2 = 0.f;
+          const int full = nblk / kRtSeg;
+          for (int w = 0; w < full; ++w) acc2 += s_seg[w][lane];
+          const float accf = full < kRtWaves ? s_seg[full][lane] : 0.f;
+          double s = (double)acc2 + (double)accf;
+          s += __shfl_xor(s, 16);
+          s += __shfl_xor(s, 32);
+          if (lane < 16 && mine < nc) s_mean[mine] += (double)(float)s;
+        }
+        __syncthreads();
+      }
+    }
+    for (int k = c0 + tid; k < ce; k += kRtThreads) {
+      const int slot = s_slot[k - c0];
+      if (slot < 0) continue;
+      const double mean = s_mean[slot] / (double)cnt;
+      if (scores) scores[n * k_cand + k] = (float)mean;
+      if (bk < 0 || mean < bv) {
+        bv = mean;
+        bk = k;
+      }
+    }
+    __syncthreads();
+  }
+  sv[tid] = bv;
+  si[tid] = bk;
+  __syncthreads();
+  for (int s = kRtThreads / 2; s > 0; s >>= 1) {
+    if (tid < s) {
+      const double v2 = sv[tid + s];
+      const int k2 = si[tid + s];
+      const int k1 = si[tid];
+      if (k2 >= 0 && (k1 < 0 || v2 < sv[tid] || (v2 == sv[tid] && k2 < k1))) {
+        sv[tid] = v2;
+        si[tid] = k2;
       }
     }
     __syncthreads();
@@ -242,12 +481,9 @@ __global__ __launch_bounds__(kRtThreads) void k_rt_select(int k_cand, int kp, do
   const double u[3] = {(double)cand[kb], (double)cand[kp + kb], (double)cand[2 * kp + kb]};
   const double* row = rowd + (int64_t)kRtRow * n;
   int v = 0;
-  for (int it = i0; it < i1; ++it) {
-    const int4 rec = items[it];
-    for (int m = threadIdx.x; m < rec.z; m += kRtThreads) {
-      const int64_t s = (int64_t)rec.y + m;
-      v += cheirality_vote(row, x1[s], y1[s], x2[s], y2[s], u, tau);
-    }
+  for (int m = tid; m < cnt; m += kRtThreads) {
+    const int64_t s = start + m;
+    v += cheirality_vote(row, x1[s], y1[s], x2[s], y2[s], u, tau);
   }
   __syncthreads();
   si[threadIdx.x] = v;
@@ -482,34 +718,39 @@ hipError_t launch_rt_pairs(hipStream_t st, int64_t n_pairs, const int32_t* pair_
 template <bool CAP>
 hipError_t launch_rt_score_t(hipStream_t st, int64_t n_items, int n_groups, const int4* items, const float* rowf,
                              const float* x1, const float* y1, const float* x2, const float* y2, const float* cand,
-                             int kp, float tau, float* partial, hipEvent_t ev0, hipEvent_t ev1) {
+                             int n_cand, int kp, float tau, float* partial, float* item_abs, hipEvent_t ev0,
+                             hipEvent_t ev1) {
   const dim3 grid((unsigned)(n_items * n_groups)), block(kRtThreads);
   if (ev0)
     hipExtLaunchKernelGGL(k_rt_score<CAP>, grid, block, 0, st, ev0, ev1, 0, items, n_groups, rowf, x1, y1, x2, y2,
-                          cand, kp, tau, partial);
+                          cand, n_cand, kp, tau, partial, item_abs);
   else
-    k_rt_score<CAP><<<grid, block, 0, st>>>(items, n_groups, rowf, x1, y1, x2, y2, cand, kp, tau, partial);
+    k_rt_score<CAP><<<grid, block, 0, st>>>(items, n_groups, rowf, x1, y1, x2, y2, cand, n_cand, kp, tau, partial,
+                                            item_abs);
   return hipGetLastError();
 }
 
 hipError_t launch_rt_score(hipStream_t st, int64_t n_items, int n_groups, const int4* items, const float* rowf,
                            const float* x1, const float* y1, const float* x2, const float* y2, const float* cand,
-                           int kp, double tau, float* partial, hipEvent_t ev0, hipEvent_t ev1) {
+                           int n_cand, int kp, double tau, float* partial, float* item_abs, hipEvent_t ev0,
+                           hipEvent_t ev1) {
   if (n_items == 0) return hipSuccess;
   if (std::isinf(tau))
-    return launch_rt_score_t<false>(st, n_items, n_groups, items, rowf, x1, y1, x2, y2, cand, kp, 0.f, partial, ev0,
-                                    ev1);
-  return launch_rt_score_t<true>(st, n_items, n_groups, items, rowf, x1, y1, x2, y2, cand, kp, (float)tau, partial,
-                                 ev0, ev1);
+    return launch_rt_score_t<false>(st, n_items, n_groups, items, rowf, x1, y1, x2, y2, cand, n_cand, kp, 0.f,
+                                    partial, item_abs, ev0, ev1);
+  return launch_rt_score_t<true>(st, n_items, n_groups, items, rowf, x1, y1, x2, y2, cand, n_cand, kp, (float)tau,
+                                 partial, item_abs, ev0, ev1);
 }
 
 hipError_t launch_rt_select(hipStream_t st, int64_t n_pairs, int k, int kp, double tau, const int32_t* pair_item_off,
-                            const int4* items, const float* partial, const float* cand, const double* rowd,
-                            const float* x1, const float* y1, const float* x2, const float* y2, float* scores,
-                            int32_t* best, int32_t* vote, double* t_rel, double* score_best) {
+                            const int4* items, const float* partial, const float* item_abs, const float* cand,
+                            const float* rowf, const double* rowd, const float* x1, const float* y1, const float* x2,
+                            const float* y2, float* scores, int32_t* best, int32_t* vote, double* t_rel,
+                            double* score_best) {
   if (n_pairs == 0) return hipSuccess;
-  k_rt_select<<<(unsigned)n_pairs, kRtThreads, 0, st>>>(k, kp, tau, pair_item_off, items, partial, cand, rowd, x1, y1,
-                                                        x2, y2, scores, best, vote, t_rel, score_best);
+  k_rt_select<<<(unsigned)n_pairs, kRtThreads, 0, st>>>(k, kp, tau, pair_item_off, items, partial, item_abs, cand,
+                                                        rowf, rowd, x1, y1, x2, y2, scores, best, vote, t_rel,
+                                                        score_best);
   return hipGetLastError();
 }
 
