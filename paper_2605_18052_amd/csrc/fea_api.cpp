@@ -1138,6 +1138,8 @@ void fea_destroy(fea_ctx* c) {
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   destroy_graph(c);
   if (c->stage) (void)hipHostFree(c->stage);
+  if (c->lz_host) (void)hipHostFree(c->lz_host);
+  if (c->lz_ev) (void)hipEventDestroy(c->lz_ev);
   if (c->loss_log) (void)hipHostFree(c->loss_log);
   if (c->inl_log) (void)hipHostFree(c->inl_log);
   if (c->judge_ok_h) (void)hipHostFree(c->judge_ok_h);
@@ -2486,6 +2488,13 @@ void camera_entries(int32_t n_cams, int64_t n_pairs, const int32_t* pi, const in
   }
 }
 
+// The other camera of each entry, so that a step reads it without the pair.
+std::vector<int32_t> entry_others(const std::vector<int32_t>& ent, const int32_t* pi, const int32_t* pj) {
+  std::vector<int32_t> oth(ent.size());
+  for (size_t e = 0; e < ent.size(); ++e) oth[e] = (ent[e] & 1) ? pi[ent[e] >> 1] : pj[ent[e] >> 1];
+  return oth;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2607,9 +2616,40 @@ fea_status fea_ta_default_options(fea_ta_options* o) {
 
 namespace {
 
-// Steps of one alignment phase: a captured graph of an even number of steps
-// (the parity, and so the buffer roles, are the same at its end as at its
-// start) replayed, then the remainder launched directly.
+// Runs `iters` iterations of `step` (which flips `parity`): a chunk of an even
+// number launched directly, the following chunks from a captured graph of as
+// many (the parity, and so the buffer roles, are the same at a chunk's end as
+// at its start), the remainder directly.  The first chunk keeps the device
+// busy (64 steps of 5 us) while the host captures and instantiates the graph
+// (200-400 us, idle time when that came first).
+template <class Step>
+hipError_t run_captured(hipStream_t st, int iters, int& parity, Step step) {
+  constexpr int kChunk = 64;
+  int done = 0;
+  hipError_t e = hipSuccess;
+  if (iters >= 2 * kChunk) {
+    for (; done < kChunk && e == hipSuccess; ++done) e = step();
+    if (e != hipSuccess) return e;
+    hipGraph_t g = nullptr;
+    hipGraphExec_t x = nullptr;
+    e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) return e;
+    hipError_t le = hipSuccess;
+    const int p0 = parity;
+    for (int k = 0; k < kChunk && le == hipSuccess; ++k) le = step();
+    e = hipStreamEndCapture(st, &g);
+    parity = p0;
+    if (le != hipSuccess) e = le;
+    if (e == hipSuccess) e = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
+    if (g) (void)hipGraphDestroy(g);
+    for (; e == hipSuccess && done + kChunk <= iters; done += kChunk) e = hipGraphLaunch(x, st);
+    if (x) (void)hipGraphExecDestroy(x);
+  }
+  for (; e == hipSuccess && done < iters; ++done) e = step();
+  return e;
+}
+
+// Steps of one alignment phase.
 struct TaPhase {
   fea_ctx* c;
   int runs, N;
@@ -2629,30 +2669,7 @@ struct TaPhase {
     return e;
   }
   hipError_t run(int iters) {
-    constexpr int kChunk = 64;
-    int done = 0;
-    if (iters >= 2 * kChunk) {
-      hipGraph_t g = nullptr;
-      hipGraphExec_t x = nullptr;
-      hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal);
-      if (e != hipSuccess) return e;
-      hipError_t le = hipSuccess;
-      const int p0 = parity;
-      for (int k = 0; k < kChunk && le == hipSuccess; ++k) le = step();
-      e = hipStreamEndCapture(c->stream, &g);
-      parity = p0;
-      if (le != hipSuccess) e = le;
-      if (e == hipSuccess) e = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
-      if (g) (void)hipGraphDestroy(g);
-      for (; e == hipSuccess && done + kChunk <= iters; done += kChunk) e = hipGraphLaunch(x, c->stream);
-      if (x) (void)hipGraphExecDestroy(x);
-      if (e != hipSuccess) return e;
-    }
-    for (; done < iters; ++done) {
-      hipError_t e = step();
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return run_captured(c->stream, iters, parity, [this] { return step(); });
   }
 };
 
@@ -2691,9 +2708,7 @@ fea_status fea_translation_align(fea_ctx* c, int32_t n_cams, int64_t n_pairs, co
   if (!all_finite(o_init, r3)) return fail(c, FEA_ENONFINITE, "non-finite initial centre");
   std::vector<int32_t> off, ent;
   camera_entries(n_cams, n_pairs, pair_i, pair_j, off, ent);
-  // the other camera of each entry, so that a step reads it without the pair
-  std::vector<int32_t> oth(ent.size());
-  for (size_t e = 0; e < ent.size(); ++e) oth[e] = (ent[e] & 1) ? pair_i[ent[e] >> 1] : pair_j[ent[e] >> 1];
+  const std::vector<int32_t> oth = entry_others(ent, pair_i, pair_j);
 
   DeviceGuard g(c->device);
   CallScratch sc(c->stream);
@@ -2887,56 +2902,28 @@ fea_status fea_ra_default_options(fea_ra_options* o) {
 
 namespace {
 
-// Runs `iters` iterations of `step` (which flips `parity`), an even number
-// at a time from a captured graph, the rest launched directly.
-template <class Step>
-hipError_t run_captured(hipStream_t st, int iters, int& parity, Step step) {
-  constexpr int kChunk = 64;
-  int done = 0;
-  if (iters >= 2 * kChunk) {
-    hipGraph_t g = nullptr;
-    hipGraphExec_t x = nullptr;
-    hipError_t e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return e;
-    hipError_t le = hipSuccess;
-    const int p0 = parity;
-    for (int k = 0; k < kChunk && le == hipSuccess; ++k) le = step();
-    e = hipStreamEndCapture(st, &g);
-    parity = p0;
-    if (le != hipSuccess) e = le;
-    if (e == hipSuccess) e = hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
-    if (g) (void)hipGraphDestroy(g);
-    for (; e == hipSuccess && done + kChunk <= iters; done += kChunk) e = hipGraphLaunch(x, st);
-    if (x) (void)hipGraphExecDestroy(x);
-    if (e != hipSuccess) return e;
-  }
-  for (; done < iters; ++done) {
-    hipError_t e = step();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-}  // namespace
-
-namespace {
-
-// Lanczos scratch (device arrays): basis V [(kmax+1) x n], the step's vector
-// w [n], the apply kernel's per-camera side output sq [n], both passes'
-// projections h1, h2, the tridiagonal alpha, beta, the Ritz coefficients s
-// [kmax+1] and the norm partials.
+// Lanczos scratch (device arrays): basis V [(kmax+1) x n], the vectors of
+// alternate steps w [2][n], both passes' projections h1, h2, the tridiagonal
+// alpha, beta, the Ritz coefficients s [kmax+1] and the norm partials; the
+// tridiagonal's copy in pinned host memory and the event it has landed by.
 struct LzScratch {
   int64_t n = 0;
   int kmax = 0;
-  double *V = nullptr, *w = nullptr, *sq = nullptr, *h1 = nullptr, *h2 = nullptr, *alpha = nullptr,
-         *beta = nullptr, *s = nullptr, *part = nullptr;
+  double *V = nullptr, *w[2] = {nullptr, nullptr}, *h1 = nullptr, *h2 = nullptr, *alpha = nullptr, *beta = nullptr,
+         *s = nullptr, *part = nullptr;
+  double* ab_h = nullptr;  // [2][kLzSteps]
+  hipEvent_t ev = nullptr;
 };
+constexpr int kLzSteps = 256;  // most steps between restarts
+constexpr int kLzCheck = 16;   // steps between looks at the tridiagonal
+// Steps queued past a look before the host waits for it: the device runs them
+// while the host takes the eigenvalue (60-100 us; a step is ~22 us).  If the
+// look ends the iteration they are not used.
+constexpr int kLzAhead = 4;
 
 // A = wm M + wp diag(c1 c1^T) over the pair graph (device arrays).
 struct LzOperator {
-  int n_cams;
-  const int32_t *cam_off, *cam_ent, *pair_i, *pair_j;
-  const double* Rrel;
+  fea::LzGraph g;
   const double* c1;
   double wm, wp;
 };
@@ -3040,38 +3027,67 @@ hipError_t lanczos_bottom(hipStream_t st, const LzOperator& A, double sigma, con
   double theta_prev = std::numeric_limits<double>::quiet_NaN();
   std::vector<double> a, b;
   for (;;) {
-    int m = 0;
-    bool done = false;
+    // at most `most` steps from this start; `run` of them queued, the first
+    // half of step `run` (its product, which completes step run - 1) too when
+    // half is set
+    const int most = (int)std::min<int64_t>(z.kmax, (int64_t)max_apply - applied);
+    int run = 0, m = 0;
+    bool half = false, done = false;
     double theta = 0.0;
-    for (int j = 0; j < z.kmax; ++j) {
-      e = fea::launch_lz_step(st, A.n_cams, A.cam_off, A.cam_ent, A.pair_i, A.pair_j, A.Rrel, A.c1, A.wm, A.wp, z.V,
-                              j, z.w, z.sq, z.h1, z.h2, z.part, z.alpha, z.beta);
-      if (e != hipSuccess) return e;
-      ++applied;
-      m = j + 1;
-      if (m % 16 != 0 && m != z.kmax && applied < max_apply) continue;
-      a.assign(m, 0.0);
-      b.assign(m, 0.0);
-      if ((e = hipMemcpyAsync(a.data(), z.alpha, m * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-          (e = hipMemcpyAsync(b.data(), z.beta, m * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-          (e = hipStreamSynchronize(st)) != hipSuccess)
+    auto apply = [&](int j) {
+      return fea::launch_lz_apply(st, A.g, A.c1, A.wm, A.wp, z.V, j, z.w[(j + 1) & 1], z.w[j & 1], z.h1, z.h2, z.part,
+                                  z.alpha, z.beta);
+    };
+    auto orth = [&](int j) {
+      return fea::launch_lz_orthogonalise(st, n, z.V, j, z.w[j & 1], z.h1, z.h2, z.part, z.alpha, z.beta);
+    };
+    auto run_to = [&](int steps) {
+      hipError_t r = hipSuccess;
+      for (; run < steps && r == hipSuccess; ++run) {
+        if (!half) r = apply(run);
+        half = false;
+        if (r == hipSuccess) r = orth(run);
+      }
+      return r;
+    };
+    while (!done && m < z.kmax) {
+      m = (int)std::min<int64_t>((int64_t)(m / kLzCheck + 1) * kLzCheck, most);
+      if (most <= 0) m = 1;  // a bound of zero products still takes one
+      if ((e = run_to(m)) != hipSuccess) return e;
+      // step m - 1 completed by the next step's product or, at the last
+      // one, by a launch of its own
+      if (fea::lz_fused_next(n) && run == m) {
+        if (m < most) {
+          e = apply(m);
+          half = true;
+        } else {
+          e = fea::launch_lz_finish(st, n, z.V, m - 1, z.w[(m - 1) & 1], z.h1, z.h2, z.part, z.alpha, z.beta);
+        }
+        if (e != hipSuccess) return e;
+      }
+      if ((e = hipMemcpyAsync(z.ab_h, z.alpha, m * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+          (e = hipMemcpyAsync(z.ab_h + kLzSteps, z.beta, m * sizeof(double), hipMemcpyDeviceToHost, st)) !=
+              hipSuccess ||
+          (e = hipEventRecord(z.ev, st)) != hipSuccess)
         return e;
+      if ((e = run_to(std::min(m + kLzAhead, most))) != hipSuccess) return e;
+      if ((e = hipEventSynchronize(z.ev)) != hipSuccess) return e;
+      a.assign(z.ab_h, z.ab_h + m);
+      b.assign(z.ab_h + kLzSteps, z.ab_h + kLzSteps + m);
       theta = tridiag_smallest(a, b, m);
       const bool exhausted = !(b[m - 1] > 1e-14 * sigma);
       const bool settled = std::fabs(theta - theta_prev) <= 3e-5 * std::fabs(theta) + 1e-12 * sigma;
       theta_prev = theta;
-      if (exhausted || settled || applied >= max_apply) {
-        done = true;
-        break;
-      }
+      done = exhausted || settled || applied + m >= max_apply;
     }
+    applied += m;
     // the Ritz vector of the basis built so far
     const std::vector<double> sv = tridiag_eigvec(a, b, m, theta);
     if ((e = hipMemcpyAsync(z.s, sv.data(), m * sizeof(double), hipMemcpyHostToDevice, st)) != hipSuccess) return e;
-    if ((e = fea::launch_lz_combine(st, n, m, z.V, z.s, done ? y : z.w)) != hipSuccess) return e;
+    if ((e = fea::launch_lz_combine(st, n, m, z.V, z.s, done ? y : z.w[0])) != hipSuccess) return e;
     if (done) return hipStreamSynchronize(st);
     // restart from it (a unit vector: the basis is orthonormal)
-    if ((e = hipMemcpyAsync(z.V, z.w, n * sizeof(double), hipMemcpyDeviceToDevice, st)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(z.V, z.w[0], n * sizeof(double), hipMemcpyDeviceToDevice, st)) != hipSuccess) return e;
   }
 }
 
@@ -3103,20 +3119,24 @@ fea_status fea_rotation_averaging(fea_ctx* c, int32_t n_cams, int64_t n_pairs, c
   if (a6_init && !all_finite(a6_init, (size_t)6 * n_cams)) return fail(c, FEA_ENONFINITE, "non-finite a6_init");
   std::vector<int32_t> off, ent;
   camera_entries(n_cams, n_pairs, pair_i, pair_j, off, ent);
+  const std::vector<int32_t> oth = entry_others(ent, pair_i, pair_j);
   int32_t max_deg = 0;
   for (int32_t i = 0; i < n_cams; ++i) max_deg = std::max(max_deg, off[i + 1] - off[i]);
   const size_t N3 = (size_t)3 * n_cams, N6 = (size_t)6 * n_cams;
 
   DeviceGuard g(c->device);
   CallScratch sc(c->stream);
-  int32_t *dpi, *dpj, *doff, *dent, *derr;
-  double *dR, *col, *c1, *a6[2], *m, *v, *dloss;
+  int32_t *dpi, *dpj, *doff, *dent, *doth, *derr;
+  double *dR, *dRent, *ddist, *col, *c1, *a6[2], *m, *v, *dloss;
   fea::TaCounters* ctr;
   HIP_OR_FAIL(c, sc.put(dpi, pair_i, (size_t)n_pairs));
   HIP_OR_FAIL(c, sc.put(dpj, pair_j, (size_t)n_pairs));
   HIP_OR_FAIL(c, sc.put(doff, off.data(), off.size()));
   HIP_OR_FAIL(c, sc.put(dent, ent.data(), ent.size()));
+  HIP_OR_FAIL(c, sc.put(doth, oth.data(), oth.size()));
   HIP_OR_FAIL(c, sc.put(dR, R_rel, (size_t)9 * n_pairs));
+  HIP_OR_FAIL(c, sc.alloc(dRent, (size_t)18 * n_pairs));
+  HIP_OR_FAIL(c, sc.alloc(ddist, (size_t)n_pairs));
   HIP_OR_FAIL(c, sc.alloc(col, N3));  // the column being solved for
   HIP_OR_FAIL(c, sc.alloc(c1, N3));
   HIP_OR_FAIL(c, sc.alloc(a6[0], N6));
@@ -3136,6 +3156,8 @@ fea_status fea_rotation_averaging(fea_ctx* c, int32_t n_cams, int64_t n_pairs, c
   }
   hipError_t e = hipSuccess;
   if (ev[0]) e = hipEventRecord(ev[0], c->stream);
+  const fea::LzGraph graph{n_cams, doff, dent, doth, dRent};
+  if (e == hipSuccess) e = fea::launch_ra_entries(c->stream, n_cams, doff, dent, dR, dRent);
   if (a6_init) {
     if (e == hipSuccess)
       e = hipMemcpyAsync(a6[0], a6_init, N6 * sizeof(double), hipMemcpyHostToDevice, c->stream);
@@ -3146,25 +3168,29 @@ fea_status fea_rotation_averaging(fea_ctx* c, int32_t n_cams, int64_t n_pairs, c
     const double sig1 = 2.0 * max_deg, sig2 = 2.0 * (max_deg / (double)n_pairs + 0.5 / n_cams);
     LzScratch z;
     z.n = (int64_t)N3;
-    z.kmax = (int)std::min<int64_t>({256, z.n, std::max<int64_t>(o.init_iters, 1)});
+    z.kmax = (int)std::min<int64_t>({kLzSteps, z.n, std::max<int64_t>(o.init_iters, 1)});
     if (e == hipSuccess) e = sc.alloc(z.V, (size_t)(z.kmax + 1) * N3);
-    if (e == hipSuccess) e = sc.alloc(z.w, N3);
-    if (e == hipSuccess) e = sc.alloc(z.sq, N3);
+    if (e == hipSuccess) e = sc.alloc(z.w[0], N3);
+    if (e == hipSuccess) e = sc.alloc(z.w[1], N3);
     if (e == hipSuccess) e = sc.alloc(z.h1, (size_t)z.kmax + 1);
     if (e == hipSuccess) e = sc.alloc(z.h2, (size_t)z.kmax + 1);
     if (e == hipSuccess) e = sc.alloc(z.alpha, (size_t)z.kmax + 1);
     if (e == hipSuccess) e = sc.alloc(z.beta, (size_t)z.kmax + 1);
     if (e == hipSuccess) e = sc.alloc(z.s, (size_t)z.kmax + 1);
     if (e == hipSuccess) e = sc.alloc(z.part, (size_t)fea::lz_orth_blocks(z.n));
+    if (e == hipSuccess && !c->lz_host)
+      e = hipHostMalloc(reinterpret_cast<void**>(&c->lz_host), 2 * kLzSteps * sizeof(double), hipHostMallocDefault);
+    if (e == hipSuccess && !c->lz_ev) e = hipEventCreateWithFlags(&c->lz_ev, hipEventDisableTiming);
+    z.ab_h = c->lz_host;
+    z.ev = c->lz_ev;
     for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-      const LzOperator A{n_cams, doff, dent, dpi, dpj, dR, k == 0 ? nullptr : c1, k == 0 ? 1.0 : 1.0 / n_pairs,
-                         1.0 / n_cams};
+      const LzOperator A{graph, k == 0 ? nullptr : c1, k == 0 ? 1.0 : 1.0 / n_pairs, 1.0 / n_cams};
       e = lanczos_bottom(c->stream, A, k == 0 ? sig1 : sig2, v0 + (size_t)k * N3, o.init_iters, z, col);
       if (e == hipSuccess)
         e = fea::launch_ra_columns(c->stream, n_cams, col, k == 0 ? nullptr : c1, k == 0 ? c1 : a6[0], derr);
     }
   }
-  if (e == hipSuccess) e = fea::launch_ra_loss(c->stream, n_pairs, dpi, dpj, dR, a6[0], dloss);
+  if (e == hipSuccess) e = fea::launch_ra_loss(c->stream, n_pairs, dpi, dpj, dR, a6[0], ddist, dloss);
   double* dRinit = nullptr;
   if (e == hipSuccess && R_init) {
     e = sc.alloc(dRinit, (size_t)9 * n_cams);
@@ -3174,13 +3200,13 @@ fea_status fea_rotation_averaging(fea_ctx* c, int32_t n_cams, int64_t n_pairs, c
   const double decay = o.iters > 0 ? std::pow(o.lr_end_frac, 1.0 / o.iters) : 1.0;
   if (e == hipSuccess) e = fea::launch_ta_counters(c->stream, ctr, o.lr);
   auto ostep = [&]() {
-    hipError_t r = fea::launch_ra_step(c->stream, n_cams, n_pairs, doff, dent, dpi, dpj, dR, a6[par], a6[par ^ 1], m,
-                                       v, ctr, par, o.beta1, o.beta2, o.adam_eps, decay);
+    hipError_t r = fea::launch_ra_step(c->stream, graph, n_pairs, a6[par], a6[par ^ 1], m, v, ctr, par, o.beta1,
+                                       o.beta2, o.adam_eps, decay);
     par ^= 1;
     return r;
   };
   if (e == hipSuccess) e = run_captured(c->stream, o.iters, par, ostep);
-  if (e == hipSuccess) e = fea::launch_ra_loss(c->stream, n_pairs, dpi, dpj, dR, a6[par], dloss + 1);
+  if (e == hipSuccess) e = fea::launch_ra_loss(c->stream, n_pairs, dpi, dpj, dR, a6[par], ddist, dloss + 1);
   double* dRout = nullptr;
   if (e == hipSuccess) e = sc.alloc(dRout, (size_t)9 * n_cams);
   if (e == hipSuccess) e = fea::launch_ra_to_R(c->stream, n_cams, a6[par], dRout);

@@ -175,6 +175,8 @@ struct fea_ctx {
   // pinned staging ring for small host-to-device copies
   void* stage = nullptr;
   size_t stage_used = 0;
+  double* lz_host = nullptr;   // pinned host: tridiagonal entries of the rotation initialisation
+  hipEvent_t lz_ev = nullptr;  // recorded after their copy
   double* loss_log = nullptr;  // pinned host: loss at the end of each solver round (64)
 
   // kernel timing (HIP events around each per-match pass)
