@@ -2654,8 +2654,9 @@ struct TaPhase {
   fea_ctx* c;
   int runs, N;
   int64_t P;
-  const int32_t *off, *ent, *oth;
-  const double* tg;
+  const int32_t* off;
+  const int2* ent2;
+  const double* tgt;
   double* o[2];
   double *m, *v;
   fea::TaCounters* ctr;
@@ -2663,8 +2664,8 @@ struct TaPhase {
   int parity = 0;
 
   hipError_t step() {
-    hipError_t e = fea::launch_ta_step(c->stream, runs, N, P, off, ent, oth, tg, o[parity], o[parity ^ 1], m, v,
-                                       ctr, parity, b1, b2, eps, decay);
+    hipError_t e = fea::launch_ta_step(c->stream, runs, N, P, off, ent2, tgt, o[parity], o[parity ^ 1], m, v, ctr,
+                                       parity, b1, b2, eps, decay);
     parity ^= 1;
     return e;
   }
@@ -2713,7 +2714,8 @@ fea_status fea_translation_align(fea_ctx* c, int32_t n_cams, int64_t n_pairs, co
   DeviceGuard g(c->device);
   CallScratch sc(c->stream);
   int32_t *dpi, *dpj, *doff, *dent, *doth, *derr, *drun;
-  double *dR, *dt, *tg, *o0, *o1, *m, *v, *pl, *cl, *rl, *om0, *om1, *fl;
+  int2* dent2;
+  double *dR, *dt, *tg, *tgt, *o0, *o1, *m, *v, *pl, *cl, *rl, *om0, *om1, *fl;
   fea::TaCounters* ctr;
   HIP_OR_FAIL(c, sc.put(dpi, pair_i, (size_t)n_pairs));
   HIP_OR_FAIL(c, sc.put(dpj, pair_j, (size_t)n_pairs));
@@ -2724,6 +2726,8 @@ fea_status fea_translation_align(fea_ctx* c, int32_t n_cams, int64_t n_pairs, co
   HIP_OR_FAIL(c, sc.put(dt, t_rel, (size_t)3 * n_pairs));
   HIP_OR_FAIL(c, sc.put(o0, o_init, r3));
   HIP_OR_FAIL(c, sc.alloc(tg, (size_t)3 * n_pairs));
+  HIP_OR_FAIL(c, sc.alloc(dent2, (size_t)2 * n_pairs));
+  HIP_OR_FAIL(c, sc.alloc(tgt, (size_t)6 * n_pairs));
   HIP_OR_FAIL(c, sc.alloc(o1, r3));
   HIP_OR_FAIL(c, sc.alloc(m, r3));
   HIP_OR_FAIL(c, sc.alloc(v, r3));
@@ -2747,8 +2751,9 @@ fea_status fea_translation_align(fea_ctx* c, int32_t n_cams, int64_t n_pairs, co
   hipError_t e = hipSuccess;
   if (ev[0]) e = hipEventRecord(ev[0], c->stream);
   if (e == hipSuccess) e = fea::launch_ta_targets(c->stream, n_pairs, dpj, dR, dt, tg);
+  if (e == hipSuccess) e = fea::launch_ta_entries(c->stream, n_cams, doff, dent, doth, tg, dent2, tgt);
   // the runs, side by side
-  TaPhase ph{c, n_runs, n_cams, n_pairs, doff, dent, doth, tg, {o0, o1}, m, v, ctr,
+  TaPhase ph{c, n_runs, n_cams, n_pairs, doff, dent2, tgt, {o0, o1}, m, v, ctr,
              o.beta1, o.beta2, o.adam_eps, o.iters_run > 0 ? std::pow(o.lr_end_frac, 1.0 / o.iters_run) : 1.0};
   if (e == hipSuccess) e = fea::launch_ta_counters(c->stream, ctr, o.lr);
   if (e == hipSuccess) e = ph.run(o.iters_run);
@@ -2759,7 +2764,7 @@ fea_status fea_translation_align(fea_ctx* c, int32_t n_cams, int64_t n_pairs, co
   // the merged centres, one more loop
   if (e == hipSuccess) e = hipMemsetAsync(m, 0, n3 * sizeof(double), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(v, 0, n3 * sizeof(double), c->stream);
-  TaPhase fin{c, 1, n_cams, n_pairs, doff, dent, doth, tg, {om0, om1}, m, v, ctr,
+  TaPhase fin{c, 1, n_cams, n_pairs, doff, dent2, tgt, {om0, om1}, m, v, ctr,
               o.beta1, o.beta2, o.adam_eps, o.iters_final > 0 ? std::pow(o.lr_end_frac, 1.0 / o.iters_final) : 1.0};
   if (e == hipSuccess) e = fea::launch_ta_counters(c->stream, ctr, o.lr_final);
   if (e == hipSuccess) e = fin.run(o.iters_final);

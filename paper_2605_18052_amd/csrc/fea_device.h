@@ -227,6 +227,16 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return a[0];
 }
 
+// t plus the lanes' values 0..c-1 (c <= 64, the other lanes' zero) added one
+// after another in lane order, the same for every lane: the serial sum of a
+// list whose elements were loaded side by side.
+__device__ __forceinline__ double wave_serial_sum(double t, double v, int c) {
+  for (int q = 0; q < c; q += 8)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t += readlane_f64(v, q + u);
+  return t;
+}
+
 __device__ __forceinline__ double readfirstlane_f64(double v) {
   const int lo = __builtin_amdgcn_readfirstlane(__double2loint(v));
   const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(v));

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kRaThreads) void k_ra_entries(int n_cams, const int
                                                            const double* __restrict__ Rrel,
                                                            double* __restrict__ Rent) {
   const int lane = threadIdx.x & 63;
-  const int w = blockIdx.x * kRaWaves + (threadIdx.x >> 6);
+  const int w = blockIdx.x * kRaWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= n_cams) return;
   const int e0 = cam_off[w], deg = cam_off[w + 1] - e0;
   double* out = Rent + 9 * (int64_t)e0;
@@ -68,13 +68,8 @@ __device__ __forceinline__ double mul_rounded(double a, double b) {
 // The sum of part[0..nparts) in index order, the same for every lane.
 __device__ __forceinline__ double parts_sum(const double* __restrict__ part, int nparts, int lane) {
   double t = 0.0;
-  for (int q0 = 0; q0 < nparts; q0 += 64) {
-    const double v = q0 + lane < nparts ? part[q0 + lane] : 0.0;
-    const int c = min(64, nparts - q0);
-    for (int q = 0; q < c; q += 8)  // past the last part zeros are added
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t += readlane_f64(v, q + u);
-  }
+  for (int q0 = 0; q0 < nparts; q0 += 64)
+    t = wave_serial_sum(t, q0 + lane < nparts ? part[q0 + lane] : 0.0, min(64, nparts - q0));
   return t;
 }
 
@@ -98,7 +93,7 @@ __global__ __launch_bounds__(kRaThreads) void k_ra_apply(int n_cams, const int32
                                                          double* __restrict__ vnext, double* __restrict__ alpha,
                                                          double* __restrict__ beta) {
   const int lane = threadIdx.x & 63;
-  const int w = blockIdx.x * kRaWaves + (threadIdx.x >> 6);
+  const int w = blockIdx.x * kRaWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= n_cams) return;
   const int e0 = cam_off[w], deg = cam_off[w + 1] - e0;
   double cw[3] = {c_in[3 * w], c_in[3 * w + 1], c_in[3 * w + 2]};
@@ -185,7 +180,7 @@ __global__ void k_ra_columns(int n_cams, const double* __restrict__ c, const dou
 // One Adam step on the 6D parameters of every camera.  Latency-bound: one
 // wave per camera, its entries' loads one level deep (entry -> other camera's
 // parameters; a pair table between them made it two).  1,000 cameras, 21
-// pairs each: 5.53 -> 4.89 us.
+// pairs each: 5.58 -> 5.22 us.
 __global__ __launch_bounds__(kRaThreads) void k_ra_step(int n_cams, int64_t n_pairs, const int32_t* __restrict__ cam_off,
                                                         const int32_t* __restrict__ cam_ent,
                                                         const int32_t* __restrict__ ent_other,
@@ -195,7 +190,7 @@ __global__ __launch_bounds__(kRaThreads) void k_ra_step(int n_cams, int64_t n_pa
                                                         TaCounters* ctr, int p, double beta1, double beta2,
                                                         double eps, double decay) {
   const int lane = threadIdx.x & 63;
-  const int w = blockIdx.x * kRaWaves + (threadIdx.x >> 6);
+  const int w = blockIdx.x * kRaWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double lr = ctr->lr[p];
   const double b1t = ctr->b1t[p] * beta1, b2t = ctr->b2t[p] * beta2;
   if (w == 0 && lane == 0) {  // the other parity's slot: read by the next step only
@@ -216,8 +211,13 @@ __global__ __launch_bounds__(kRaThreads) void k_ra_step(int n_cams, int64_t n_pa
   }
   const double inv_np = 1.0 / (double)n_pairs;
   const double* __restrict__ Rw = Rent + 9 * (int64_t)e0;
-  double Ra[9];  // this camera's rotation
-  rot6d_forward(a_cur, Ra);
+  // this camera's rotation and the frame its gradient goes back through,
+  // formed while the entries load
+  const Rot6dFrame fr = rot6d_frame(a_cur);
+  const double* b1 = fr.b1;
+  const double* b2 = fr.b2;
+  const double Ra[9] = {b1[0], b2[0], b1[1] * b2[2] - b1[2] * b2[1], b1[1], b2[1], b1[2] * b2[0] - b1[0] * b2[2],
+                        b1[2], b2[2], b1[0] * b2[1] - b1[1] * b2[0]};
   double G[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   for (int k = lane; k < deg; k += 64) {
     const int ent = cam_ent[e0 + k], oc = ent_other[e0 + k];
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(kRaThreads) void k_ra_step(int n_cams, int64_t n_pa
   wave_sum_f64_scatter(G);
   if (lane >= 6) return;
   double ga[6];
-  rot6d_vjp(a_cur, G, ga);
+  rot6d_vjp(fr, a_cur, G, ga);
   double gk = ga[0], ak = a_cur[0];
   for (int k = 1; k < 6; ++k)
     if (lane == k) {
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kLzThreads) void k_lz_dots(int64_t n, const double*
 // wavefronts instead of n / 64; the 16 partial sums are added in LDS in a
 // fixed order.  part[block] = the block's sum of w^2 after the subtraction.
 // A latency chain: eight rows' loads are in flight together (one at a time:
-// 4.14 us a launch at 1,000 cameras, now 3.56; the projections 5.39 -> 3.29).
+// 4.0 us a launch at 1,000 cameras, now 3.6-3.8; the projections 5.3 -> 3.5).
 __global__ __launch_bounds__(kLzOrthThreads * kLzOrthWaves) void k_lz_orth(int64_t n, int m,
                                                                           const double* __restrict__ V,
                                                                           const double* __restrict__ h,
