@@ -47,17 +47,22 @@ __global__ __launch_bounds__(kLossThreads) void k_item_loss(int64_t n_items, con
   }
 }
 
-// Threads [0, N): dL/da6 = vjp of the 6D map, dL/dt, scaled by gout.
-// Threads [N, N+G): dL/dlog f of each group = sum over its cameras of
-// f_c dL/df_c, scaled by gout.
-__global__ void k_param_grad(int N, int G, const double* __restrict__ a6, const double* __restrict__ gR,
-                             const double* __restrict__ gt_in, const double* __restrict__ gf,
-                             const double* __restrict__ F, const int32_t* __restrict__ grp_off,
-                             const int32_t* __restrict__ grp_cams, const double* __restrict__ gout,
-                             double* __restrict__ ga6, double* __restrict__ gt, double* __restrict__ glogf) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+// The first ceil(N / kGradThreads) workgroups, one thread per camera: dL/da6 =
+// vjp of the 6D map, and dL/dt, scaled by gout.  The others, one wavefront
+// per group: dL/dlog f = sum over its cameras of f_c dL/df_c, scaled by gout.
+// One group of 500 cameras: 75 -> 7.4 us.
+constexpr int kGradThreads = 256;
+
+__global__ __launch_bounds__(kGradThreads) void k_param_grad(
+    int N, int G, const double* __restrict__ a6, const double* __restrict__ gR, const double* __restrict__ gt_in,
+    const double* __restrict__ gf, const double* __restrict__ F, const int32_t* __restrict__ grp_off,
+    const int32_t* __restrict__ grp_cams, const double* __restrict__ gout, double* __restrict__ ga6,
+    double* __restrict__ gt, double* __restrict__ glogf) {
+  const int cam_blocks = (N + kGradThreads - 1) / kGradThreads;
   const double s = gout ? gout[0] : 1.0;
-  if (k < N) {
+  if ((int)blockIdx.x < cam_blocks) {
+    const int k = blockIdx.x * kGradThreads + threadIdx.x;
+    if (k >= N) return;
     double a[6], g[9], ga[6];
 #pragma unroll
     for (int q = 0; q < 6; ++q) a[q] = a6[6 * k + q];
@@ -70,15 +75,15 @@ __global__ void k_param_grad(int N, int G, const double* __restrict__ a6, const 
     if (gt)
 #pragma unroll
       for (int q = 0; q < 3; ++q) gt[3 * k + q] = s * gt_in[3 * k + q];
-  } else if (k < N + G) {
-    const int g = k - N;
-    double acc = 0.0;
-    for (int q = grp_off[g]; q < grp_off[g + 1]; ++q) {
-      const int c = grp_cams[q];
-      acc += gf[c] * F[c];
-    }
-    if (glogf) glogf[g] = s * acc;
+    return;
   }
+  __shared__ double2 s_buf[kGradThreads];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = ((int)blockIdx.x - cam_blocks) * (kGradThreads / kWave) + wave;
+  if (g >= G || !glogf) return;  // uniform per wave
+  const int lane = threadIdx.x & 63;
+  const double acc = group_focal_grad(grp_off[g], grp_off[g + 1], grp_cams, gf, F, lane, s_buf + wave * kWave);
+  if (lane == 0) glogf[g] = s * acc;
 }
 
 }  // namespace
@@ -96,8 +101,10 @@ hipError_t launch_item_loss(fea_ctx* c, double* loss_out) {
 
 hipError_t launch_param_grad(fea_ctx* c, const double* a6, const double* gout, double* ga6, double* gt,
                              double* glogf) {
-  const int total = c->N + c->G;
-  k_param_grad<<<(unsigned)((total + 255) / 256), 256, 0, c->stream>>>(
+  constexpr int groups_per_block = kGradThreads / kWave;
+  const unsigned blocks = (unsigned)((c->N + kGradThreads - 1) / kGradThreads) +
+                          (unsigned)((c->G + groups_per_block - 1) / groups_per_block);
+  k_param_grad<<<blocks, kGradThreads, 0, c->stream>>>(
       c->N, c->G, a6, c->gR.as<double>(), c->gt.as<double>(), c->gf.as<double>(), c->Fe.as<double>(),
       c->d_grp_off.as<int32_t>(), c->d_grp_cams.as<int32_t>(), gout, ga6, gt, glogf);
   return hipGetLastError();

@@ -237,6 +237,44 @@ __device__ __forceinline__ double wave_serial_sum(double t, double v, int c) {
   return t;
 }
 
+// dL/dlog f of an intrinsics group, by one wavefront: f_c dL/df_c added over
+// the group's cameras grp_cams[b, e) one after another (one fused
+// multiply-add each), the same for every lane.  A thread that walks the list
+// waits for two dependent loads per camera (500 cameras in one group: 75 us);
+// here 64 cameras are loaded side by side, the next 64 in flight while the
+// chain reads a block from LDS (7.4 us; 18.5 us with readlanes instead, which
+// cost four and two moves per camera), and the order of the additions is the
+// list's either way.  buf: kWave entries of the wavefront's own.
+__device__ __forceinline__ double group_focal_grad(int b, int e, const int32_t* __restrict__ grp_cams,
+                                                   const double* __restrict__ gf, const double* __restrict__ F,
+                                                   int lane, double2* buf) {
+  double s = 0.0;
+  double2 next = make_double2(0.0, 0.0);  // past the end: fma(0, 0, s) = s
+  if (b + lane < e) {
+    const int c = grp_cams[b + lane];
+    next = make_double2(gf[c], F[c]);
+  }
+  for (int k = b; k < e; k += kWave) {
+    buf[lane] = next;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    next = make_double2(0.0, 0.0);
+    if (k + kWave + lane < e) {
+      const int c = grp_cams[k + kWave + lane];
+      next = make_double2(gf[c], F[c]);
+    }
+    const int n = min(e - k, kWave);
+    for (int q = 0; q < n; q += 16) {
+      double2 v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = buf[q + u];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s = fma(v[u].x, v[u].y, s);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  return s;
+}
+
 __device__ __forceinline__ double readfirstlane_f64(double v) {
   const int lo = __builtin_amdgcn_readfirstlane(__double2loint(v));
   const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(v));
