@@ -320,7 +320,7 @@ hipError_t run_ablation(fea_ctx* c, int variant, int reps, double* ms, float* pa
   if (e == hipSuccess && variant == 0) {
     const int64_t t = c->P * kPartStride;
     k_abl_item_to_pair<<<(unsigned)((t + 255) / 256), 256, 0, c->stream>>>(
-        (int32_t)c->P, c->pair_item_off.as<int32_t>(), c->part.as<double>(), pair_sum_dev);
+        (int32_t)c->P, c->pair_runs.as<int32_t>(), c->part.as<double>(), pair_sum_dev);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);

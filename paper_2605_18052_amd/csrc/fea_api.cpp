@@ -80,9 +80,8 @@ void dfree(DBuf& b) {
 // when the ring is full the stream is drained and the ring reused.
 constexpr size_t kStageBytes = 16u << 20;
 
-hipError_t stage_copy(fea_ctx* c, void* dst, const void* src, size_t bytes) {
-  if (bytes == 0) return hipSuccess;
-  if (bytes > kStageBytes) return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream);
+// `bytes` (at most kStageBytes) of the ring, valid until it wraps.
+hipError_t stage_take(fea_ctx* c, size_t bytes, void** out) {
   hipError_t e = hipSuccess;
   if (!c->stage) {
     if ((e = hipHostMalloc(&c->stage, kStageBytes, hipHostMallocDefault)) != hipSuccess) {
@@ -96,8 +95,17 @@ hipError_t stage_copy(fea_ctx* c, void* dst, const void* src, size_t bytes) {
     if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
     c->stage_used = 0;
   }
-  uint8_t* p = static_cast<uint8_t*>(c->stage) + c->stage_used;
+  *out = static_cast<uint8_t*>(c->stage) + c->stage_used;
   c->stage_used += need;
+  return hipSuccess;
+}
+
+hipError_t stage_copy(fea_ctx* c, void* dst, const void* src, size_t bytes) {
+  if (bytes == 0) return hipSuccess;
+  if (bytes > kStageBytes) return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream);
+  void* p = nullptr;
+  const hipError_t e = stage_take(c, bytes, &p);
+  if (e != hipSuccess) return e;
   std::memcpy(p, src, bytes);
   return hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, c->stream);
 }
@@ -127,7 +135,7 @@ std::vector<DBuf*> all_bufs(fea_ctx* c) {
       v.push_back(&c->lay_block[b]);
     v.push_back(&c->lpos[b]);
   }
-  DBuf* one[] = {&c->seg_ws, &c->perm, &c->swp, &c->item_rec, &c->d_scene_item_off, &c->scene_loss, &c->pair_item_off,
+  DBuf* one[] = {&c->seg_ws, &c->perm, &c->swp, &c->item_rec, &c->d_scene_item_off, &c->scene_loss, &c->pair_runs, &c->pair_ws, &c->d_cam_code,
                  &c->item_keep, &c->item_base, &c->part, &c->d_pair_i, &c->d_pair_j, &c->d_cam_off,
                  &c->d_cam_ent, &c->d_group, &c->d_grp_off, &c->d_grp_cams, &c->d_cx, &c->d_cy, &c->a6,
                  &c->tp, &c->logf, &c->m_a6, &c->v_a6, &c->m_t, &c->v_t, &c->m_f, &c->v_f, &c->R[0],
@@ -221,9 +229,6 @@ double median(std::vector<double> v) {
   return (n % 2) ? v[n / 2] : 0.5 * (v[n / 2 - 1] + v[n / 2]);
 }
 
-// Work items of the current layout: runs of <= tile matches of one pair
-// (pairs with no retained match get none), and each camera's int4 entries
-// {2n+side, first item, end item, other camera} for the epilogue.
 // No scene converged (start of a solve, new scenes).
 hipError_t clear_convergence(fea_ctx* c) {
   c->n_done = 0;
@@ -237,61 +242,58 @@ hipError_t clear_convergence(fea_ctx* c) {
   return e;
 }
 
+// Work items of the current layout: runs of <= tile matches of one pair
+// (pairs with no retained match get none), and each camera's int4 entries
+// {2n+side, first item, end item, other camera} for the epilogue.  The host
+// counts the items; the tables are written on the device.
 hipError_t build_items(fea_ctx* c) {
-  const int64_t tile = fea::tile_matches_of(c->tile_cfg);
-  c->h_item_pair.clear();
-  c->h_item_start.clear();
-  c->h_item_count.clear();
-  c->h_pair_item_off.assign(c->P + 1, 0);
-  for (int64_t n = 0; n < c->P; ++n) {
-    c->h_pair_item_off[n] = (int32_t)c->h_item_pair.size();
-    for (int64_t s = 0; s < c->cur_len[n]; s += tile) {
-      c->h_item_pair.push_back((int32_t)n);
-      c->h_item_start.push_back((int32_t)(c->phys_off[n] + s));
-      c->h_item_count.push_back((int32_t)std::min<int64_t>(tile, c->cur_len[n] - s));
-    }
+  const int64_t P = c->P, tile = fea::tile_matches_of(c->tile_cfg);
+  c->h_pair_runs.resize(3 * P + 1);
+  int32_t *first = c->h_pair_runs.data(), *start = first + P + 1, *len = start + P;
+  int64_t n_items = 0;
+  for (int64_t n = 0; n < P; ++n) {
+    first[n] = (int32_t)n_items;
+    start[n] = (int32_t)c->phys_off[n];
+    len[n] = (int32_t)c->cur_len[n];
+    n_items += (c->cur_len[n] + tile - 1) / tile;
   }
-  c->h_pair_item_off[c->P] = (int32_t)c->h_item_pair.size();
-  c->n_items = (int64_t)c->h_item_pair.size();
-  c->h_item_rec.assign(4 * c->n_items, 0);
-  const bool flags = c->n_done > 0 && (int)c->scene_done_h.size() == c->S;
-  for (int64_t it = 0; it < c->n_items; ++it) {
-    c->h_item_rec[4 * it] = c->h_item_pair[it];
-    c->h_item_rec[4 * it + 1] = c->h_item_start[it];
-    c->h_item_rec[4 * it + 2] = c->h_item_count[it];
-    // items of converged scenes are skipped by the steps
-    c->h_item_rec[4 * it + 3] = flags && c->scene_done_h[c->pair_scene[c->h_item_pair[it]]] != 0 ? 1 : 0;
-  }
-  c->h_cam_ent4.assign(4 * 2 * c->P, 0);
-  for (size_t e = 0; e < c->cam_ent.size(); ++e) {
-    const int32_t code = c->cam_ent[e];
-    const int64_t n = code >> 1;
-    const int side = code & 1;
-    c->h_cam_ent4[4 * e] = code;
-    c->h_cam_ent4[4 * e + 1] = c->h_pair_item_off[n];
-    c->h_cam_ent4[4 * e + 2] = c->h_pair_item_off[n + 1];
-    c->h_cam_ent4[4 * e + 3] = side ? c->pair_i[n] : c->pair_j[n];
-  }
-  hipError_t e;
-  if ((e = upload(c, c->item_rec, c->h_item_rec.data(), c->h_item_rec.size())) != hipSuccess) return e;
+  first[P] = (int32_t)n_items;
+  c->n_items = n_items;
   // items of each scene: pairs are sorted by their first camera, so when a
   // scene's cameras have contiguous ids its items are a contiguous range
   c->scene_items_contiguous = true;
-  for (int64_t it = 1; it < c->n_items; ++it)
-    if (c->pair_scene[c->h_item_pair[it]] < c->pair_scene[c->h_item_pair[it - 1]]) c->scene_items_contiguous = false;
-  std::vector<int32_t> soff(c->S + 1, (int32_t)c->n_items);
-  for (int64_t it = c->n_items - 1; it >= 0; --it) soff[c->pair_scene[c->h_item_pair[it]]] = (int32_t)it;
+  std::vector<int32_t> soff(c->S + 1, (int32_t)n_items);
+  int32_t later = c->S;  // scene of the next pair that has items
+  for (int64_t n = P - 1; n >= 0; --n) {
+    if (first[n + 1] == first[n]) continue;
+    const int32_t sc = c->pair_scene[n];
+    if (sc > later) c->scene_items_contiguous = false;
+    later = sc;
+    soff[sc] = first[n];
+  }
   for (int sc = c->S - 1; sc >= 0; --sc) soff[sc] = std::min(soff[sc], soff[sc + 1]);
+  const size_t items = (size_t)std::max<int64_t>(n_items, 1);
+  hipError_t e;
+  if ((e = dalloc(c->item_rec, items * 4 * sizeof(int32_t))) != hipSuccess) return e;
+  if ((e = dalloc(c->d_cam_ent, (size_t)std::max<int64_t>(2 * P, 1) * 4 * sizeof(int32_t))) != hipSuccess) return e;
   if ((e = upload(c, c->d_scene_item_off, soff.data(), soff.size())) != hipSuccess) return e;
   if ((e = dalloc(c->scene_loss, (size_t)std::max(c->S, 1) * sizeof(double))) != hipSuccess) return e;
-  if ((e = upload(c, c->pair_item_off, c->h_pair_item_off.data(), c->P + 1)) != hipSuccess) return e;
-  if ((e = upload(c, c->d_cam_ent, c->h_cam_ent4.data(), c->h_cam_ent4.size())) != hipSuccess) return e;
-  if ((e = dalloc(c->qpart, std::max<int64_t>(c->n_items, 1) * 36 * sizeof(double))) != hipSuccess) return e;
-  if ((e = dalloc(c->part, std::max<int64_t>(c->n_items, 1) * fea::kPartStride * sizeof(double))) != hipSuccess)
-    return e;
-  if ((e = dalloc(c->item_keep, std::max<int64_t>(c->n_items, 1) * sizeof(int32_t))) != hipSuccess) return e;
-  if ((e = dalloc(c->item_wsum, std::max<int64_t>(c->n_items, 1) * sizeof(double))) != hipSuccess) return e;
-  return dalloc(c->item_base, std::max<int64_t>(c->n_items, 1) * 2 * sizeof(int32_t));
+  if ((e = upload(c, c->pair_runs, c->h_pair_runs.data(), c->h_pair_runs.size())) != hipSuccess) return e;
+  // items of converged scenes are skipped by the steps
+  if ((e = fea::launch_items(c, c->n_done > 0 && (int)c->scene_done_h.size() == c->S)) != hipSuccess) return e;
+  if ((e = dalloc(c->qpart, items * 36 * sizeof(double))) != hipSuccess) return e;
+  if ((e = dalloc(c->part, items * fea::kPartStride * sizeof(double))) != hipSuccess) return e;
+  if ((e = dalloc(c->item_keep, items * sizeof(int32_t))) != hipSuccess) return e;
+  if ((e = dalloc(c->item_wsum, items * sizeof(double))) != hipSuccess) return e;
+  return dalloc(c->item_base, items * 2 * sizeof(int32_t));
+}
+
+// Scene of every item, in item order, for the host's sums over items of
+// scenes whose items interleave.
+template <class F>
+void for_items_of_scenes(const fea_ctx* c, F f) {
+  for (int64_t n = 0; n < c->P; ++n)
+    for (int32_t it = c->h_pair_runs[n]; it < c->h_pair_runs[n + 1]; ++it) f(it, c->pair_scene[n]);
 }
 
 // Every scene may use learned weights again, no rejection counted.
@@ -563,12 +565,12 @@ fea_status load_matches_common(fea_ctx* c, int64_t n, const float* x1, const flo
     c->cam_off[c->pair_j[k] + 1]++;
   }
   for (int i = 0; i < N; ++i) c->cam_off[i + 1] += c->cam_off[i];
-  c->cam_ent.assign(2 * c->P, 0);
-  std::vector<int32_t> fill(c->cam_off.begin(), c->cam_off.end() - 1);
+  std::vector<int32_t> code(2 * c->P), fill(c->cam_off.begin(), c->cam_off.end() - 1);
   for (int64_t k = 0; k < c->P; ++k) {
-    c->cam_ent[fill[c->pair_i[k]]++] = (int32_t)(2 * k);
-    c->cam_ent[fill[c->pair_j[k]]++] = (int32_t)(2 * k + 1);
+    code[fill[c->pair_i[k]]++] = (int32_t)(2 * k);
+    code[fill[c->pair_j[k]]++] = (int32_t)(2 * k + 1);
   }
+  HIP_OR_FAIL(c, upload(c, c->d_cam_code, code.data(), code.size()));
   HIP_OR_FAIL(c, upload(c, c->d_pair_i, c->pair_i.data(), c->P));
   HIP_OR_FAIL(c, upload(c, c->d_pair_j, c->pair_j.data(), c->P));
   HIP_OR_FAIL(c, upload(c, c->d_cam_off, c->cam_off.data(), N + 1));
@@ -722,37 +724,42 @@ hipError_t set_counters(fea_ctx* c, int64_t t, int64_t g) {
 // matches that pass the snapshot threshold (mask == nullptr; the pose table
 // must hold this round's F_hat and tau) or whose sorted position is set in the
 // device bit mask.  Leaves the new layout live with its per-pair lengths.
+//
+// The new lengths, offsets and the items' destinations are formed on the
+// device, so the scatter follows the count at once; the host reads the
+// lengths meanwhile and prepares the new layout's items.
 hipError_t compact_layout(fea_ctx* c, const uint32_t* mask) {
+  const int64_t P = c->P;
   hipError_t e = fea::launch_filter_count(c, mask);
+  if (e == hipSuccess) e = dalloc(c->pair_ws, (size_t)fea::filter_offsets_ints(P) * sizeof(int32_t));
+  if (e == hipSuccess) e = fea::launch_filter_lengths(c);
   if (e != hipSuccess) return e;
-  std::vector<int32_t> keep;
-  if ((e = download(c, keep, c->item_keep, c->n_items)) != hipSuccess) return e;
-  // new per-pair lengths, aligned offsets and per-item destinations; the
-  // last item of each pair also gets the aligned end of the pair's run, up
-  // to which it clears the padding
-  std::vector<int64_t> new_len(c->P, 0), new_off(c->P, 0);
-  std::vector<int32_t> base(2 * c->n_items, -1);
-  for (int64_t n = 0; n < c->P; ++n)
-    for (int32_t it = c->h_pair_item_off[n]; it < c->h_pair_item_off[n + 1]; ++it) new_len[n] += keep[it];
-  int64_t off = 0;
-  for (int64_t n = 0; n < c->P; ++n) {
-    new_off[n] = off;
-    int64_t run = off;
-    for (int32_t it = c->h_pair_item_off[n]; it < c->h_pair_item_off[n + 1]; ++it) {
-      base[2 * it] = (int32_t)run;
-      run += keep[it];
-    }
-    off += (new_len[n] + fea::kAlign - 1) / fea::kAlign * fea::kAlign;
-    if (c->h_pair_item_off[n + 1] > c->h_pair_item_off[n]) base[2 * (c->h_pair_item_off[n + 1] - 1) + 1] = (int32_t)off;
+  // the lengths, through the pinned ring where they fit
+  std::vector<int32_t> len;
+  void* staged = nullptr;
+  const size_t bytes = (size_t)P * sizeof(int32_t);
+  if (bytes > 0 && bytes <= kStageBytes) {
+    if ((e = stage_take(c, bytes, &staged)) != hipSuccess) return e;
+    if (!c->len_ev && (e = hipEventCreateWithFlags(&c->len_ev, hipEventDisableTiming)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(staged, c->pair_ws.p, bytes, hipMemcpyDeviceToHost, c->stream)) != hipSuccess) return e;
+    if ((e = hipEventRecord(c->len_ev, c->stream)) != hipSuccess) return e;
+  } else if ((e = download(c, len, c->pair_ws, (size_t)P)) != hipSuccess) {
+    return e;
   }
   const int dst = (c->cur == 1) ? 2 : 1;
-  if ((e = upload(c, c->item_base, base.data(), base.size())) != hipSuccess) return e;
+  if ((e = fea::launch_filter_offsets(c)) != hipSuccess) return e;
   if ((e = fea::launch_filter_scatter(c, dst, mask)) != hipSuccess) return e;
-  // no wait: later work on the stream sees the new layout in order, and the
-  // host builds the work items meanwhile
+  if (staged && (e = hipEventSynchronize(c->len_ev)) != hipSuccess) return e;
+  // no wait for the scatter: later work on the stream sees the new layout in
+  // order
+  const int32_t* new_len = staged ? static_cast<const int32_t*>(staged) : len.data();
+  int64_t off = 0;
+  for (int64_t n = 0; n < P; ++n) {
+    c->cur_len[n] = new_len[n];
+    c->phys_off[n] = off;
+    off += (c->cur_len[n] + fea::kAlign - 1) / fea::kAlign * fea::kAlign;
+  }
   c->cur = dst;
-  c->cur_len = new_len;
-  c->phys_off = new_off;
   c->layout_len = off;
   return hipSuccess;
 }
@@ -770,7 +777,7 @@ hipError_t quad_round(fea_ctx* c) {
     // per-scene counts and normalisers on the device: no host round trip
     if ((e = fea::launch_scene_z(c)) != hipSuccess) return e;
     c->host_z_stale = true;
-    return fea::launch_quad_reduce(c, c->pair_item_off.as<int32_t>());
+    return fea::launch_quad_reduce(c, c->pair_runs.as<int32_t>());
   }
   std::vector<int32_t> keep;
   if ((e = download(c, keep, c->item_keep, c->n_items)) != hipSuccess) return e;
@@ -778,7 +785,7 @@ hipError_t quad_round(fea_ctx* c) {
   const bool frozen = c->opt.converge_deg > 0 && c->n_done > 0 && (int)c->Zs.size() == c->S &&
                       (int)c->scene_done_h.size() == c->S;
   std::vector<int64_t> zs(c->S, 0);
-  for (int64_t it = 0; it < c->n_items; ++it) zs[c->pair_scene[c->h_item_pair[it]]] += keep[it];
+  for_items_of_scenes(c, [&](int64_t it, int sc) { zs[sc] += keep[it]; });
   if ((int)c->Zs.size() != c->S) c->Zs.assign(c->S, 0);
   for (int sc = 0; sc < c->S; ++sc)
     if (!(frozen && c->scene_done_h[sc] != 0)) c->Zs[sc] = zs[sc];
@@ -793,14 +800,14 @@ hipError_t quad_round(fea_ctx* c) {
     std::vector<double> ws;
     if ((e = download(c, ws, c->item_wsum, c->n_items)) != hipSuccess) return e;
     std::vector<double> zw(c->S, 0.0);
-    for (int64_t it = 0; it < c->n_items; ++it) zw[c->pair_scene[c->h_item_pair[it]]] += ws[it];
+    for_items_of_scenes(c, [&](int64_t it, int sc) { zw[sc] += ws[it]; });
     if ((int)c->inv_zw_h.size() != c->S) c->inv_zw_h.assign(c->S, 0.f);
     for (int sc = 0; sc < c->S; ++sc)
       if (!(frozen && c->scene_done_h[sc] != 0)) c->inv_zw_h[sc] = zw[sc] > 0 ? (float)(1.0 / zw[sc]) : 0.f;
     if ((e = upload(c, c->d_inv_zw, c->inv_zw_h.data(), c->S)) != hipSuccess) return e;
   }
   c->host_z_stale = false;
-  return fea::launch_quad_reduce(c, c->pair_item_off.as<int32_t>());
+  return fea::launch_quad_reduce(c, c->pair_runs.as<int32_t>());
 }
 
 // Per-scene weighting mode of the round (chosen now, or kept as restored
@@ -839,7 +846,7 @@ hipError_t round_weights(fea_ctx* c, bool choose_mode) {
   std::vector<double> ws;
   if ((e = download(c, ws, c->item_wsum, c->n_items)) != hipSuccess) return e;
   std::vector<double> zw(c->S, 0.0);
-  for (int64_t it = 0; it < c->n_items; ++it) zw[c->pair_scene[c->h_item_pair[it]]] += ws[it];
+  for_items_of_scenes(c, [&](int64_t it, int sc) { zw[sc] += ws[it]; });
   c->inv_zw_h.assign(c->S, 0.f);
   for (int sc = 0; sc < c->S; ++sc) c->inv_zw_h[sc] = zw[sc] > 0 ? (float)(1.0 / zw[sc]) : 0.f;
   return upload(c, c->d_inv_zw, c->inv_zw_h.data(), c->S);
@@ -1140,6 +1147,7 @@ void fea_destroy(fea_ctx* c) {
   if (c->stage) (void)hipHostFree(c->stage);
   if (c->lz_host) (void)hipHostFree(c->lz_host);
   if (c->lz_ev) (void)hipEventDestroy(c->lz_ev);
+  if (c->len_ev) (void)hipEventDestroy(c->len_ev);
   if (c->loss_log) (void)hipHostFree(c->loss_log);
   if (c->inl_log) (void)hipHostFree(c->inl_log);
   if (c->judge_ok_h) (void)hipHostFree(c->judge_ok_h);
@@ -1576,11 +1584,10 @@ fea_status plain_loss_per_scene(fea_ctx* c, const double* R, const double* T, co
   // scenes with interleaved camera ids: sum the item losses on the host
   std::vector<double> part, sum(c->S, 0.0), sum_snap(c->S, 0.0);
   HIP_OR_FAIL(c, download(c, part, c->part, (size_t)c->n_items * fea::kPartStride));
-  for (int64_t it = 0; it < c->n_items; ++it) {
-    const int sc = c->pair_scene[c->h_item_pair[it]];
+  for_items_of_scenes(c, [&](int64_t it, int sc) {
     sum[sc] += part[it * fea::kPartStride + 9];
     sum_snap[sc] += part[it * fea::kPartStride + 8];
-  }
+  });
   HIP_OR_FAIL(c, upload(c, out, sum.data(), (size_t)c->S));
   HIP_OR_FAIL(c, upload(c, out_snap, sum_snap.data(), (size_t)c->S));
   return FEA_OK;

@@ -51,18 +51,16 @@ struct fea_ctx {
   int64_t P = 0;
   std::vector<int32_t> pair_i, pair_j;  // lexicographic pair table
   std::vector<int64_t> seg_off;         // full sorted ranges [P+1]
-  std::vector<int32_t> cam_off, cam_ent;  // camera -> (pair*2 + side)
+  std::vector<int32_t> cam_off;  // camera -> its entries [N+1]
   std::vector<int64_t> phys_off, cur_len;  // current layout per pair
   int64_t layout_len = 0;                  // current layout length (matches)
   int cur = 0;                             // which layout buffer is live (0 = full)
 
   // items of the current layout
   int64_t n_items = 0;
-  std::vector<int32_t> h_item_pair, h_item_start, h_item_count, h_pair_item_off;
-  std::vector<int32_t> h_item_rec;  // per item {pair, start, count, 0}
+  std::vector<int32_t> h_pair_runs;  // first item of each pair [P+1], its run's start [P] and length [P]
   int tile_cfg = 0;        // index into kTiles
   bool tile_tuned = false; // tile_cfg chosen for this set of matches
-  std::vector<int32_t> h_cam_ent4;  // per camera entry: {2n+side, item_begin, item_end, other}
 
   // scenes: a partition of the cameras into independent problems solved
   // together (each with its own gauge, Z, threshold and loss)
@@ -99,7 +97,10 @@ struct fea_ctx {
   fea::DBuf lpos[3];     // int32: sorted position of each layout entry (-1 = padding)
   fea::DBuf perm;        // int32 [M] input index of each sorted position
   fea::DBuf swp;         // uint8 [M]
-  fea::DBuf pair_item_off, item_keep, item_base;
+  fea::DBuf pair_runs;   // int32 [3P+1]: h_pair_runs
+  fea::DBuf item_keep, item_base;
+  fea::DBuf pair_ws;     // int32: new lengths and offsets of the pairs while a layout is compacted
+  fea::DBuf d_cam_code;  // int32 [2P]: per camera entry 2n + side
   fea::DBuf item_rec;  // int4 per item: {pair, start, count, 0}
   fea::DBuf d_scene_item_off;  // int32 [S+1]: items of each scene (contiguous)
   fea::DBuf scene_loss;        // double [S]
@@ -175,6 +176,7 @@ struct fea_ctx {
   // pinned staging ring for small host-to-device copies
   void* stage = nullptr;
   size_t stage_used = 0;
+  hipEvent_t len_ev = nullptr;  // recorded after the copy of a compaction's pair lengths
   double* lz_host = nullptr;   // pinned host: tridiagonal entries of the rotation initialisation
   hipEvent_t lz_ev = nullptr;  // recorded after their copy
   double* loss_log = nullptr;  // pinned host: loss at the end of each solver round (64)
@@ -193,6 +195,10 @@ namespace fea {
 // *bad_bits to the validation error bits.
 hipError_t segment_matches(fea_ctx* c, const float* x1, const float* y1, const float* x2, const float* y2,
                            const int32_t* cam1, const int32_t* cam2, int* bad_bits);
+hipError_t launch_items(fea_ctx* c, bool flags);
+int64_t filter_offsets_ints(int64_t n_pairs);
+hipError_t launch_filter_lengths(fea_ctx* c);
+hipError_t launch_filter_offsets(fea_ctx* c);
 hipError_t export_sorted(fea_ctx* c, int32_t cam_base, const int64_t* seg_off_dev, float* x1, float* y1,
                          float* x2, float* y2, int32_t* cam1, int32_t* cam2);
 

@@ -570,4 +570,118 @@ hipError_t segment_matches(fea_ctx* c, const float* x1, const float* y1, const f
   return alloc_filtered_layouts(c, off);
 }
 
+namespace {
+
+constexpr int kItThreads = 256;
+
+// The tables of a layout from its pairs' runs: the first pair_blocks
+// workgroups, one wavefront per pair, write the work items (runs of at most
+// `tile` matches) {pair, start, count, 1 for a stopped scene}; the others, one
+// thread each, the camera entries {2n + side, first item, end item, other
+// camera}.  12,000 items and 21,000 entries: 4.7 us; the host, which wrote
+// and copied them before, kept the device waiting (30 million matches loaded
+// and a first round begun, three layouts: 3.48 -> 3.20 ms).
+__global__ __launch_bounds__(kItThreads) void k_items(
+    int P, int pair_blocks, int tile, const int32_t* __restrict__ first, const int32_t* __restrict__ start,
+    const int32_t* __restrict__ len, const int32_t* __restrict__ pair_scene, const int32_t* __restrict__ done,
+    int4* __restrict__ items, const int32_t* __restrict__ cam_code, const int32_t* __restrict__ pair_i,
+    const int32_t* __restrict__ pair_j, int4* __restrict__ cam_ent) {
+  if ((int)blockIdx.x < pair_blocks) {
+    const int n = blockIdx.x * (kItThreads / 64) + (threadIdx.x >> 6);
+    if (n >= P) return;
+    const int b = first[n], e = first[n + 1], s = start[n], l = len[n];
+    const int flag = done != nullptr && done[pair_scene[n]] != 0 ? 1 : 0;
+    for (int it = b + (threadIdx.x & 63); it < e; it += 64) {
+      const int at = (it - b) * tile;
+      items[it] = make_int4(n, s + at, min(tile, l - at), flag);
+    }
+    return;
+  }
+  const int64_t e = ((int64_t)blockIdx.x - pair_blocks) * kItThreads + threadIdx.x;
+  if (e >= 2 * (int64_t)P) return;
+  const int code = cam_code[e], n = code >> 1;
+  cam_ent[e] = make_int4(code, first[n], first[n + 1], (code & 1) ? pair_i[n] : pair_j[n]);
+}
+
+// A compaction's new layout from the items' survivor counts, one wavefront
+// per pair: the pair's new length, and that rounded up to whole aligned
+// groups (whose exclusive scan is where its run starts).
+__global__ __launch_bounds__(kItThreads) void k_filter_lengths(int P, const int32_t* __restrict__ first,
+                                                               const int32_t* __restrict__ keep,
+                                                               int32_t* __restrict__ len, int32_t* __restrict__ off) {
+  const int n = blockIdx.x * (kItThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (n >= P) return;
+  int s = 0;
+  for (int it = first[n] + lane; it < first[n + 1]; it += 64) s += keep[it];
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
+  if (lane == 0) {
+    len[n] = s;
+    off[n] = (s + kAlign - 1) / kAlign * kAlign;
+  }
+}
+
+// Where each item's first survivor goes, and, for a pair's last item, the
+// aligned end of its run, up to which it clears the padding (-1: not the
+// last).
+__global__ __launch_bounds__(kItThreads) void k_filter_offsets(int P, const int32_t* __restrict__ first,
+                                                               const int32_t* __restrict__ keep,
+                                                               const int32_t* __restrict__ len,
+                                                               const int32_t* __restrict__ off,
+                                                               int2* __restrict__ base) {
+  const int n = blockIdx.x * (kItThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (n >= P) return;
+  const int b = first[n], e = first[n + 1];
+  int run = off[n];
+  const int end = run + (len[n] + kAlign - 1) / kAlign * kAlign;
+  for (int k = b; k < e; k += 64) {
+    const int it = k + lane;
+    const int mine = it < e ? keep[it] : 0;
+    const int inc = wave_inclusive_scan(mine);
+    if (it < e) base[it] = make_int2(run + inc - mine, it == e - 1 ? end : -1);
+    run += __shfl(inc, 63);
+  }
+}
+
+unsigned pair_waves(int64_t P) { return (unsigned)((P + kItThreads / 64 - 1) / (kItThreads / 64)); }
+
+}  // namespace
+
+// Work items and camera entries of the layout that pair_runs describes;
+// flags: items of converged scenes are marked to be skipped by the steps.
+hipError_t launch_items(fea_ctx* c, bool flags) {
+  const int64_t P = c->P;
+  if (P == 0) return hipSuccess;
+  const unsigned pair_blocks = pair_waves(P);
+  const int32_t* runs = c->pair_runs.as<int32_t>();
+  k_items<<<pair_blocks + (unsigned)((2 * P + kItThreads - 1) / kItThreads), kItThreads, 0, c->stream>>>(
+      (int)P, (int)pair_blocks, (int)tile_matches_of(c->tile_cfg), runs, runs + P + 1, runs + 2 * P + 1,
+      c->d_pair_scene.as<int32_t>(), flags ? c->d_scene_done.as<int32_t>() : nullptr, c->item_rec.as<int4>(),
+      c->d_cam_code.as<int32_t>(), c->d_pair_i.as<int32_t>(), c->d_pair_j.as<int32_t>(), c->d_cam_ent.as<int4>());
+  return hipGetLastError();
+}
+
+// pair_ws: new lengths [P], new offsets [P], scratch of their scan.
+int64_t filter_offsets_ints(int64_t n_pairs) { return 2 * n_pairs + scan_scratch_ints(n_pairs); }
+
+hipError_t launch_filter_lengths(fea_ctx* c) {
+  const int64_t P = c->P;
+  if (P == 0) return hipSuccess;
+  int32_t* ws = c->pair_ws.as<int32_t>();
+  k_filter_lengths<<<pair_waves(P), kItThreads, 0, c->stream>>>((int)P, c->pair_runs.as<int32_t>(),
+                                                                c->item_keep.as<int32_t>(), ws, ws + P);
+  return hipGetLastError();
+}
+
+hipError_t launch_filter_offsets(fea_ctx* c) {
+  const int64_t P = c->P;
+  if (P == 0) return hipSuccess;
+  int32_t* ws = c->pair_ws.as<int32_t>();
+  const hipError_t e = device_exclusive_scan(ws + P, P, ws + 2 * P, c->stream);
+  if (e != hipSuccess) return e;
+  k_filter_offsets<<<pair_waves(P), kItThreads, 0, c->stream>>>(
+      (int)P, c->pair_runs.as<int32_t>(), c->item_keep.as<int32_t>(), ws, ws + P, c->item_base.as<int2>());
+  return hipGetLastError();
+}
+
 }  // namespace fea
