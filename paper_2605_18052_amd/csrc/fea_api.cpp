@@ -1407,23 +1407,27 @@ fea_status put_poses(fea_ctx* c, const double* R, const double* t, const double*
     for (int k = 0; k < 3; ++k)
       tt[3 * i + k] = -(Rc[9 * i + 3 * k] * on[0] + Rc[9 * i + 3 * k + 1] * on[1] + Rc[9 * i + 3 * k + 2] * on[2]);
   }
-  HIP_OR_FAIL(c, upload(c, c->a6, a6.data(), 6 * N));
-  HIP_OR_FAIL(c, upload(c, c->tp, tt.data(), 3 * N));
-  HIP_OR_FAIL(c, upload(c, c->R[c->pcur], Rc.data(), 9 * N));
-  HIP_OR_FAIL(c, upload(c, c->T[c->pcur], tt.data(), 3 * N));
+  // through the pinned ring, which holds them at any number of cameras; no
+  // wait, as the ring keeps them until the stream has passed
+  static_assert((size_t)20 * 65535 * sizeof(double) <= kStageBytes, "poses of 65,535 cameras and as many groups");
+  void* staged = nullptr;
+  HIP_OR_FAIL(c, stage_take(c, ((size_t)19 * N + c->G) * sizeof(double), &staged));
+  double* src = static_cast<double*>(staged);
+  std::copy(a6.begin(), a6.end(), src);
+  std::copy(tt.begin(), tt.end(), src + 6 * N);
+  std::copy(Rc.begin(), Rc.end(), src + 9 * N);
   if (f) {
     // one focal length per group: geometric mean of its cameras' values
-    std::vector<double> logf(c->G, 0.0), fc(N);
+    double *fc = src + 18 * N, *logf = src + 19 * N;
     for (int gi = 0; gi < c->G; ++gi) {
       const int b = c->grp_off[gi], e = c->grp_off[gi + 1];
+      logf[gi] = 0.0;
       for (int k = b; k < e; ++k) logf[gi] += std::log(f[c->grp_cams[k]]);
       if (e > b) logf[gi] /= (e - b);
     }
     for (int i = 0; i < N; ++i) fc[i] = std::exp(logf[c->group[i]]);
-    HIP_OR_FAIL(c, upload(c, c->Fc[c->pcur], fc.data(), N));
-    HIP_OR_FAIL(c, upload(c, c->logf, logf.data(), c->G));
   }
-  HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
+  HIP_OR_FAIL(c, fea::launch_put_poses(c, src, f != nullptr));
   return FEA_OK;
 }
 
@@ -1485,17 +1489,8 @@ fea_status fea_residual_grad(fea_ctx* c, double* loss_dev, double* gR_dev, doubl
                                            c->Fc[c->pcur].as<double>(), false));
     HIP_OR_FAIL(c, fea::launch_resgrad(c));
   }
-  HIP_OR_FAIL(c, fea::launch_camgrad(c, 0, quad));
-  HIP_OR_FAIL(c, fea::launch_loss_sum(c));
-  const size_t N = c->N;
-  if (loss_dev)
-    HIP_OR_FAIL(c, hipMemcpyAsync(loss_dev, c->loss.p, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-  if (gR_dev)
-    HIP_OR_FAIL(c, hipMemcpyAsync(gR_dev, c->gR.p, 9 * N * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-  if (gt_dev)
-    HIP_OR_FAIL(c, hipMemcpyAsync(gt_dev, c->gt.p, 3 * N * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-  if (gf_dev)
-    HIP_OR_FAIL(c, hipMemcpyAsync(gf_dev, c->gf.p, N * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+  HIP_OR_FAIL(c, fea::launch_camgrad(c, 0, quad, gR_dev, gt_dev, gf_dev));
+  if (loss_dev) HIP_OR_FAIL(c, fea::launch_loss_sum(c, loss_dev));
   return FEA_OK;
 }
 

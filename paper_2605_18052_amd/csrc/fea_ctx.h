@@ -214,13 +214,15 @@ hipError_t launch_filter_count(fea_ctx* c, const uint32_t* mask);
 hipError_t launch_filter_scatter(fea_ctx* c, int dst, const uint32_t* mask);
 
 // --- per-camera epilogue (fea_camera.hip) ---
-hipError_t launch_camgrad(fea_ctx* c, int do_update, bool quad);
+hipError_t launch_put_poses(fea_ctx* c, const double* src, bool with_f);
+hipError_t launch_camgrad(fea_ctx* c, int do_update, bool quad, double* gR = nullptr, double* gt = nullptr,
+                          double* gf = nullptr);
 hipError_t launch_quad_build(fea_ctx* c);
 hipError_t launch_mask_init(fea_ctx* c);
 hipError_t launch_mask_slots(fea_ctx* c, int32_t* slot_pos);
 hipError_t launch_quad_reduce(fea_ctx* c, const int32_t* pair_item_off_dev);
 hipError_t launch_focal_update(fea_ctx* c);
-hipError_t launch_loss_sum(fea_ctx* c);
+hipError_t launch_loss_sum(fea_ctx* c, double* out = nullptr);
 hipError_t launch_judge(fea_ctx* c);
 hipError_t launch_choose_mode(fea_ctx* c, bool enabled);
 hipError_t launch_round_start(fea_ctx* c, bool shift, bool first, bool zero);
