@@ -593,7 +593,9 @@ fea_status fea_get_rotation_log(fea_ctx *ctx, double *R_log, int32_t *n_logged);
  * call, HIP events).  FEA_EINVAL for invalid sizes, pairs or options;
  * FEA_ENONFINITE for non-finite input; FEA_EDEGENERATE if a camera's column
  * vanishes in the initialisation (a camera without pairs).  Device scratch of
- * O(n_pairs + 257 * 3 n_cams) doubles is allocated and freed by the call. */
+ * O(n_pairs + 257 * 3 n_cams) doubles: what the stage calls need, up to 256
+ * MiB of it, stays with the context for the next such call; the rest is
+ * allocated and freed by the call. */
 typedef struct {
   int32_t init_iters; /* at most this many Lanczos steps per column (default 200000) */
   int32_t iters;      /* Adam steps (1000) */
@@ -663,7 +665,8 @@ fea_status fea_focal_vote(fea_ctx *ctx, int32_t n_cams, int64_t n_pairs, const i
  * n_cand outside [1, 2^22], candidates that are not unit vectors (1e-6) or
  * focal lengths <= 0 or tau_px <= 0; FEA_ENONFINITE for non-finite input.  Device scratch
  * (n_cand rounded up to 512, times the number of 2048-match work items, in
- * fp32) is allocated and freed by the call. */
+ * fp32) up to 256 MiB stays with the context, the rest is allocated and freed
+ * by the call. */
 fea_status fea_relative_translations(fea_ctx *ctx, const double *R, const double *f, double tau_px, int32_t n_cand,
                                      const double *cand, double *t_rel, int32_t *best, int32_t *vote,
                                      double *score_best, float *scores, float *score_ms);
@@ -690,7 +693,8 @@ fea_status fea_relative_translations(fea_ctx *ctx, const double *R, const double
  * FEA_EINVAL for invalid sizes, pairs or options (n_runs in [1, 64]),
  * FEA_ENONFINITE for non-finite input, FEA_EDEGENERATE for a zero relative
  * translation or a run whose centres all coincide.  Device scratch of
- * O(n_runs * (n_cams + n_pairs)) is allocated and freed by the call. */
+ * O(n_runs * (n_cams + n_pairs)) up to 256 MiB stays with the context, the
+ * rest is allocated and freed by the call. */
 typedef struct {
   int32_t iters_run;   /* Adam steps of every run (default 1500) */
   int32_t iters_final; /* Adam steps on the merged centres (500) */

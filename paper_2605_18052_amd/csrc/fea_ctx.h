@@ -173,6 +173,8 @@ struct fea_ctx {
   int graph_pcur = -1;
   uint64_t graph_gen = 0;  // device-buffer generation the graph was captured at
 
+  std::vector<fea::DBuf> call_mem;  // blocks that calls take their scratch from, kept between calls
+
   // pinned staging ring for small host-to-device copies
   void* stage = nullptr;
   size_t stage_used = 0;
