@@ -140,7 +140,7 @@ std::vector<DBuf*> all_bufs(fea_ctx* c) {
                  &c->d_cam_ent, &c->d_group, &c->d_grp_off, &c->d_grp_cams, &c->d_cx, &c->d_cy, &c->a6,
                  &c->tp, &c->logf, &c->m_a6, &c->v_a6, &c->m_t, &c->v_t, &c->m_f, &c->v_f, &c->R[0],
                  &c->R[1], &c->T[0], &c->T[1], &c->Fc[0], &c->Fc[1], &c->Rh, &c->Th, &c->Fh, &c->gR,
-                 &c->gt, &c->gf, &c->loss_cam, &c->loss, &c->logR, &c->errflag, &c->wait_state, &c->Re, &c->Te, &c->Fe, &c->d_pair_scene, &c->d_inv_z, &c->d_tau, &c->ptab, &c->qpart, &c->qW, &c->qmask, &c->stab, &c->counters,
+                 &c->gt, &c->gf, &c->loss_cam, &c->logR, &c->errflag, &c->wait_state, &c->Re, &c->Te, &c->Fe, &c->d_pair_scene, &c->d_inv_z, &c->d_tau, &c->ptab, &c->qpart, &c->qW, &c->qmask, &c->stab, &c->counters,
                  &c->Rh1, &c->Th1, &c->Fh1, &c->Rh2, &c->Th2, &c->Fh2, &c->d_fbar, &c->mlp, &c->wlay,
                  &c->item_wsum, &c->d_inv_zw, &c->d_scene_mode, &c->d_fbar_hist, &c->d_scene_cam_off, &c->d_scene_cams, &c->d_scene_z, &c->a6h, &c->tph, &c->logfh, &c->d_learned_ok, &c->d_fallbacks, &c->d_judge_l0, &c->d_judge_l1};
   for (DBuf* b : one) v.push_back(b);
@@ -332,7 +332,7 @@ hipError_t alloc_scene_arrays(fea_ctx* c) {
   if ((e = dalloc(c->d_fbar, 3 * (size_t)c->S * sizeof(float))) != hipSuccess) return e;
   if ((e = dalloc(c->d_fbar_hist, 3 * (size_t)c->S * sizeof(double))) != hipSuccess) return e;
   if ((e = dalloc(c->d_tau, (size_t)c->S * sizeof(double))) != hipSuccess) return e;
-  if ((e = dalloc(c->d_scene_z, ((size_t)c->S + 1) * sizeof(int64_t))) != hipSuccess) return e;
+  if ((e = dalloc(c->d_scene_z, (size_t)c->S * sizeof(int64_t))) != hipSuccess) return e;
   if ((e = dalloc(c->d_scene_done, (size_t)c->S * sizeof(int32_t))) != hipSuccess) return e;
   if ((e = dalloc(c->d_scene_change, (size_t)c->S * sizeof(double))) != hipSuccess) return e;
   if ((e = dalloc(c->d_learned_ok, (size_t)c->S * sizeof(int32_t))) != hipSuccess) return e;
@@ -374,9 +374,10 @@ hipError_t refresh_round_host(fea_ctx* c) {
   }
   if (c->host_z_stale) {
     std::vector<int64_t> z;
-    if ((e = download(c, z, c->d_scene_z, (size_t)c->S + 1)) != hipSuccess) return e;
-    c->Zs.assign(z.begin(), z.begin() + c->S);
-    c->Z = z[c->S];
+    if ((e = download(c, z, c->d_scene_z, (size_t)c->S)) != hipSuccess) return e;
+    c->Zs.assign(z.begin(), z.end());
+    c->Z = 0;
+    for (int64_t v : z) c->Z += v;
     if (c->learned_any && (e = download(c, c->inv_zw_h, c->d_inv_zw, c->S)) != hipSuccess) return e;
     c->host_z_stale = false;
   }
@@ -707,10 +708,10 @@ fea_status run_steps(fea_ctx* c, int32_t n_steps) {
   return FEA_OK;
 }
 
-// Host -> device copy of the step counters: Adam count `t` and global count
-// `g` into the slots of the current parity, and the round's learning-rate
-// factor.
-hipError_t set_counters(fea_ctx* c, int64_t t, int64_t g) {
+// The step counters at Adam count `t` and global count `g`, in the slots of
+// the current parity, with the round's learning-rate factor; and their copy
+// to the device.
+fea::StepCounters step_counters(const fea_ctx* c, int64_t t, int64_t g) {
   fea::StepCounters h;
   std::memset(&h, 0, sizeof(h));
   h.adam_t[c->pcur] = t;
@@ -718,6 +719,11 @@ hipError_t set_counters(fea_ctx* c, int64_t t, int64_t g) {
   h.b1t[c->pcur] = std::pow(c->opt.beta1, (double)t);
   h.b2t[c->pcur] = std::pow(c->opt.beta2, (double)t);
   h.lr_scale = c->lr_scale;
+  return h;
+}
+
+hipError_t set_counters(fea_ctx* c, int64_t t, int64_t g) {
+  const fea::StepCounters h = step_counters(c, t, g);
   return stage_copy(c, c->counters.p, &h, sizeof(h));
 }
 
@@ -831,7 +837,8 @@ hipError_t round_weights(fea_ctx* c, bool choose_mode) {
       c->scene_mode[sc] = (enabled && c->scene_learned_ok[sc]) ? 1 : 0;
       c->learned_any = c->learned_any || c->scene_mode[sc];
     }
-    e = fea::launch_choose_mode(c, enabled);
+    // the round start has set the modes where it ran on the device
+    if (c->max_scene_cams > fea::kMaxSceneCams) e = fea::launch_choose_mode(c, enabled);
   } else {
     c->learned_any = false;
     for (int sc = 0; sc < c->S; ++sc) c->learned_any = c->learned_any || c->scene_mode[sc];
@@ -872,13 +879,16 @@ fea_status begin_round(fea_ctx* c, double tau_px, bool sync) {
   }
   c->prev_tau_px = tau_px;
   // snapshot and its history (learned features), round parameters for the
-  // judge's restore, and (new objective) fresh Adam moments -- one kernel
+  // judge's restore, (new objective) fresh Adam moments and the step counters
+  // -- one kernel
   const bool zero = c->opt.reset_moments || c->round < 0;
-  HIP_OR_FAIL(c, fea::launch_round_start(c, c->round >= 0, c->round < 0, zero));
   if (zero) c->adam_t = 0;
+  c->lr_scale = std::pow(c->opt.lr_decay, (double)(c->round + 1));
+  HIP_OR_FAIL(c, fea::launch_round_start(c, c->round >= 0, c->round < 0, zero,
+                                         step_counters(c, c->adam_t, c->global_step)));
   if (c->max_scene_cams <= fea::kMaxSceneCams) {
     // thresholds and focal-length medians on the device: no host round trip
-    HIP_OR_FAIL(c, fea::launch_scene_tau(c, tau_px, c->round < 0));
+    HIP_OR_FAIL(c, fea::launch_scene_tau(c, tau_px, c->round < 0, c->opt.weight_mode == 1 && c->have_mlp));
     c->host_tau_stale = true;
   } else {
     HIP_OR_FAIL(c, refresh_round_host(c));
@@ -928,8 +938,6 @@ fea_status begin_round(fea_ctx* c, double tau_px, bool sync) {
     HIP_OR_FAIL(c, choose_tile(c));
     HIP_OR_FAIL(c, build_items(c));
   }
-  c->lr_scale = std::pow(c->opt.lr_decay, (double)(c->round + 1));
-  HIP_OR_FAIL(c, set_counters(c, c->adam_t, c->global_step));
   // per match, the layout changed: recapture on the next run of steps.  The
   // quadratic form's steps read only per-pair forms and device counters, so
   // its captured graph stays valid across rounds.
@@ -1120,7 +1128,7 @@ fea_status fea_create(fea_ctx** out, int32_t device, const fea_options* opt, voi
     }
     c->own_stream = true;
   }
-  if (dalloc(c->errflag, sizeof(int)) != hipSuccess || dalloc(c->loss, sizeof(double)) != hipSuccess ||
+  if (dalloc(c->errflag, sizeof(int)) != hipSuccess ||
       dalloc(c->wait_state, 2 * sizeof(unsigned)) != hipSuccess) {
     fea_destroy(c);
     return FEA_ENOMEM;
@@ -1641,24 +1649,15 @@ fea_status fea_epipolar_adjust(fea_ctx* c, fea_report* out) {
       if ((s = judge_round(c)) != FEA_OK) return s;
     }
     if (r < 64) {
-      // into pinned memory, so the copy is queued without waiting for the
-      // round's steps
+      // into pinned memory, so the host waits for none of the round's steps
       if (!c->loss_log) HIP_OR_FAIL(c, hipHostMalloc(&c->loss_log, 64 * sizeof(double), hipHostMallocDefault));
       if (!c->inl_log) HIP_OR_FAIL(c, hipHostMalloc(&c->inl_log, 64 * sizeof(int64_t), hipHostMallocDefault));
-      if (c->host_z_stale)
-        HIP_OR_FAIL(c, hipMemcpyAsync(c->inl_log + r, c->d_scene_z.as<int64_t>() + c->S, sizeof(int64_t),
-                                      hipMemcpyDeviceToHost, c->stream));
-      else
+      HIP_OR_FAIL(c, fea::launch_round_log(c, r, c->host_z_stale));
+      if (!c->host_z_stale) {
         c->inl_log[r] = c->Z;
-      HIP_OR_FAIL(c, fea::launch_loss_sum(c));
-      HIP_OR_FAIL(c, hipMemcpyAsync(c->loss_log + r, c->loss.p, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-      HIP_OR_FAIL(c, fea::launch_scene_loss_log(c, r));
-      int64_t* zrow = c->d_scene_z_log.as<int64_t>() + (size_t)r * c->S;
-      if (c->host_z_stale)
-        HIP_OR_FAIL(c, hipMemcpyAsync(zrow, c->d_scene_z.p, (size_t)c->S * sizeof(int64_t), hipMemcpyDeviceToDevice,
-                                      c->stream));
-      else
-        HIP_OR_FAIL(c, stage_copy(c, zrow, c->Zs.data(), (size_t)c->S * sizeof(int64_t)));
+        HIP_OR_FAIL(c, stage_copy(c, c->d_scene_z_log.as<int64_t>() + (size_t)r * c->S, c->Zs.data(),
+                                  (size_t)c->S * sizeof(int64_t)));
+      }
     }
     rep.rounds_run = r + 1;
     rep.iters_run += c->opt.iters_per_round;
@@ -2120,9 +2119,7 @@ fea_status fea_set_state(fea_ctx* c, const void* buf, size_t len) {
       }
       HIP_OR_FAIL(c, upload(c, c->d_inv_z, inv.data(), S));
       // the device's per-scene counts (converged scenes keep theirs)
-      std::vector<int64_t> zd(c->Zs);
-      zd.push_back(c->Z);
-      HIP_OR_FAIL(c, upload(c, c->d_scene_z, zd.data(), zd.size()));
+      HIP_OR_FAIL(c, upload(c, c->d_scene_z, c->Zs.data(), c->Zs.size()));
     } else {
       DBuf d_bits;
       hipError_t e = upload(c, d_bits, bits.data(), bits.size());

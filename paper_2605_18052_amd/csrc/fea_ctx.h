@@ -118,7 +118,7 @@ struct fea_ctx {
   fea::DBuf a6, tp, logf, m_a6, v_a6, m_t, v_t, m_f, v_f;
   fea::DBuf R[2], T[2], Fc[2];  // derived current/next R (N*9), t (N*3), f (N)
   fea::DBuf Rh, Th, Fh;         // round snapshot
-  fea::DBuf gR, gt, gf, loss_cam, loss;
+  fea::DBuf gR, gt, gf, loss_cam;
   fea::DBuf logR;
   fea::DBuf errflag;
   fea::DBuf Re, Te, Fe;  // poses built from caller-given parameters
@@ -129,7 +129,7 @@ struct fea_ctx {
   fea::DBuf d_fbar;                       // float [3*S]: median f per scene at the 3 snapshots
   fea::DBuf d_fbar_hist;                  // double [3*S]: the same medians in fp64 (device round start)
   fea::DBuf d_scene_cam_off, d_scene_cams;  // int32 [S+1], [N]: cameras of each scene
-  fea::DBuf d_scene_z;                    // int64 [S+1]: survivors per scene, total last (quadratic form)
+  fea::DBuf d_scene_z;                    // int64 [S]: survivors per scene (quadratic form)
   int32_t max_scene_cams = 0;             // largest scene, in cameras
   bool host_tau_stale = false;            // taus, tau, fbar_hist live on the device until read back
   bool host_z_stale = false;              // Zs, Z live on the device until read back
@@ -224,16 +224,16 @@ hipError_t launch_mask_init(fea_ctx* c);
 hipError_t launch_mask_slots(fea_ctx* c, int32_t* slot_pos);
 hipError_t launch_quad_reduce(fea_ctx* c, const int32_t* pair_item_off_dev);
 hipError_t launch_focal_update(fea_ctx* c);
-hipError_t launch_loss_sum(fea_ctx* c, double* out = nullptr);
+hipError_t launch_loss_sum(fea_ctx* c, double* out);
 hipError_t launch_judge(fea_ctx* c);
 hipError_t launch_choose_mode(fea_ctx* c, bool enabled);
-hipError_t launch_round_start(fea_ctx* c, bool shift, bool first, bool zero);
-hipError_t launch_scene_tau(fea_ctx* c, double tau_px, bool first);
+hipError_t launch_round_start(fea_ctx* c, bool shift, bool first, bool zero, const StepCounters& set);
+hipError_t launch_scene_tau(fea_ctx* c, double tau_px, bool first, bool learned);
 hipError_t launch_scene_z(fea_ctx* c);
 hipError_t launch_scene_loss(fea_ctx* c, double* out = nullptr, double* out_snap = nullptr);
 hipError_t launch_scene_converge(fea_ctx* c, bool check, int32_t round);
 hipError_t launch_guard(fea_ctx* c, int32_t round);
-hipError_t launch_scene_loss_log(fea_ctx* c, int32_t round);
+hipError_t launch_round_log(fea_ctx* c, int32_t round, bool device_z);
 hipError_t run_ablation(fea_ctx* c, int variant, int reps, double* ms, float* pair_sum_dev);
 hipError_t launch_camgrad_at(fea_ctx* c, const double* R, const double* T, const double* F);
 int quad_steps_blocks(fea_ctx* c);

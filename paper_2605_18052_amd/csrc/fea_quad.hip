@@ -215,10 +215,12 @@ __global__ void k_mask_slots(int64_t n, const unsigned char* __restrict__ mask, 
 }
 
 // W_n = (1/Z of the pair's scene) * the sum of the pair's item partials in
-// item order, entry k taking sum kMonoOf.of[k]; 1/Z is the pose table's
-// (learned scenes: 1/sum of weights).
+// item order, entry k taking sum kMonoOf.of[k]; 1/Z is the scene's (learned
+// scenes: 1/sum of weights).
 __global__ __launch_bounds__(kQuadThreads) void k_quad_reduce(int32_t P, const int32_t* __restrict__ pair_item_off,
-                                                              const double* __restrict__ ptab,
+                                                              const float* __restrict__ inv_z_scene,
+                                                              const float* __restrict__ inv_zw_scene,
+                                                              const int32_t* __restrict__ scene_mode,
                                                               const double* __restrict__ qpart,
                                                               double* __restrict__ qW,
                                                               const int32_t* __restrict__ pair_scene,
@@ -226,9 +228,9 @@ __global__ __launch_bounds__(kQuadThreads) void k_quad_reduce(int32_t P, const i
   const int64_t t = (int64_t)blockIdx.x * kQuadThreads + threadIdx.x;
   if (t >= (int64_t)P * kQuad) return;
   const int n = (int)(t / kQuad), k = (int)(t % kQuad);
-  if (scene_done != nullptr && scene_done[pair_scene[n]] != 0) return;  // keeps its last round's form
-  const double* row = ptab + (int64_t)n * kPairRow;
-  const double inv_z = row[kRowMode] != 0.0 ? row[kRowInvZw] : row[kRowInvZ];
+  const int sc = pair_scene[n];
+  if (scene_done != nullptr && scene_done[sc] != 0) return;  // keeps its last round's form
+  const double inv_z = (double)(scene_mode[sc] != 0 ? inv_zw_scene[sc] : inv_z_scene[sc]);
   const int mk = kMonoOf.of[k];
   double s = 0.0;
   for (int it = pair_item_off[n]; it < pair_item_off[n + 1]; ++it) s += qpart[(int64_t)it * kMono + mk];
@@ -275,17 +277,15 @@ hipError_t launch_mask_slots(fea_ctx* c, int32_t* slot_pos) {
   return hipGetLastError();
 }
 
-// W_n of every pair from the item sums of launch_quad_build; the pose
-// table's normalisers are refreshed first (they are set after the counts).
+// W_n of every pair from the item sums of launch_quad_build and the scenes'
+// normalisers, which are set after the counts.
 hipError_t launch_quad_reduce(fea_ctx* c, const int32_t* pair_item_off_dev) {
   if (c->P == 0) return hipSuccess;
-  hipError_t e = launch_pair_pose(c, c->R[c->pcur].as<double>(), c->T[c->pcur].as<double>(),
-                                  c->Fc[c->pcur].as<double>(), false);
-  if (e != hipSuccess) return e;
   const int64_t t = c->P * kQuad;
   k_quad_reduce<<<(unsigned)((t + kQuadThreads - 1) / kQuadThreads), kQuadThreads, 0, c->stream>>>(
-      (int32_t)c->P, pair_item_off_dev, c->ptab.as<double>(), c->qpart.as<double>(), c->qW.as<double>(),
-      c->d_pair_scene.as<int32_t>(), c->d_scene_done.as<int32_t>());
+      (int32_t)c->P, pair_item_off_dev, c->d_inv_z.as<float>(), c->d_inv_zw.as<float>(),
+      c->d_scene_mode.as<int32_t>(), c->qpart.as<double>(), c->qW.as<double>(), c->d_pair_scene.as<int32_t>(),
+      c->d_scene_done.as<int32_t>());
   return hipGetLastError();
 }
 

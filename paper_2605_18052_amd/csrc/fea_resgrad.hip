@@ -83,7 +83,8 @@ __global__ __launch_bounds__(kPairThreads) void k_pair_pose(
   row[kRowInvZw] = (double)inv_zw_scene[sc];
   row[kRowMode] = scene_mode[sc] != 0 ? 1.0 : 0.0;
   if (SNAP) {
-    pose_block(i, j, Rh, Th, Fh, cx, cy, Fp);
+    // the quadratic form's rounds ask for the snapshot's F alone
+    if (R != Rh || T != Th || Fc != Fh) pose_block(i, j, Rh, Th, Fh, cx, cy, Fp);
 #pragma unroll
     for (int k = 0; k < 9; ++k) row[kRowFh + k] = Fp[k];
     row[kRowCx + 0] = cx[i];
