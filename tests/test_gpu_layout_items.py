@@ -73,3 +73,39 @@ def test_compaction_matches_oracle(lengths, drop):
             for a, b in ((gR, gRr), (gt, gtr), (gf[:, None], gfr[:, None])):
                 ok, worst = per_camera_close(a, b)
                 assert ok, worst
+
+
+@pytest.mark.parametrize("lengths,drop", [
+    ([1, 3, 4, 63, 64, 65, 127, 129], [3]),
+    ([191, 192, 193, 255, 256, 257, 384], []),
+    ([8192 + 1, 8191, 8192 + 191], []),
+    ([2], []),
+])
+def test_quadratic_form_matches_oracle(lengths, drop):
+    """The same with the quadratic form, whose pass keeps the layout and marks
+    the retained matches, at run lengths around its trips of 64 matches, the
+    three in flight and an item of 8,192."""
+    n, R, t, f, m = _problem(lengths, drop, seed=10 + len(lengths))
+    pb = oracle.OracleProblem(*m, np.zeros(n), np.zeros(n))
+    eps = np.abs(oracle.residuals(pb, R, t, f))
+    with fastea.Context(0, fastea.default_options(gauge_normalize=0, inner_loop=1)) as ctx:
+        ctx.load_intrinsics(f, f * 0, f * 0)
+        ctx.load_matches(*m)
+        ctx.init_poses(R, t)
+        mask = np.ones(len(eps), np.uint8)
+        kept = ~np.isin(m[5], drop)
+        for q in (1.0, 0.7):
+            tau = tau_in_gap(eps, np.quantile(eps[kept], q)) if q < 1.0 else float(np.inf)
+            ctx.begin_round(tau * 500.0)
+            mask &= (eps < tau).astype(np.uint8)
+            got, z = ctx.get_mask()
+            assert z == mask.sum()
+            np.testing.assert_array_equal(got.astype(np.uint8), mask)
+            if mask.sum() == 0:
+                break
+            l, gR, gt, gf = (x.cpu().numpy() for x in ctx.residual_grad())
+            lr, gRr, gtr, gfr = oracle.loss_grad(pb, R, t, f, R, t, f, mask)
+            assert abs(l[0] - lr) <= 1e-5 * lr
+            for a, b in ((gR, gRr), (gt, gtr), (gf[:, None], gfr[:, None])):
+                ok, worst = per_camera_close(a, b)
+                assert ok, worst
