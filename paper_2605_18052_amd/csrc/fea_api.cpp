@@ -552,7 +552,7 @@ fea_status load_matches_common(fea_ctx* c, int64_t n, const float* x1, const flo
   HIP_OR_FAIL(c, upload(c, c->d_pair_scene, c->pair_scene.data(), c->P));
   HIP_OR_FAIL(c, dalloc(c->d_tau, (size_t)c->S * sizeof(double)));
   HIP_OR_FAIL(c, dalloc(c->ptab, (size_t)std::max<int64_t>(c->P, 1) * fea::kPairRow * sizeof(double)));
-  HIP_OR_FAIL(c, dalloc(c->qW, (size_t)std::max<int64_t>(c->P, 1) * 45 * sizeof(double)));
+  HIP_OR_FAIL(c, dalloc(c->qW, (size_t)std::max<int64_t>(c->P, 1) * fea::kMono * sizeof(double)));
   HIP_OR_FAIL(c, dalloc(c->qmask, (size_t)std::max<int64_t>(c->layout_len, 4)));
   c->ptab_current = false;
   HIP_OR_FAIL(c, dalloc(c->stab, (size_t)std::max<int64_t>(c->P, 1) * 40 * sizeof(double)));
@@ -1000,7 +1000,9 @@ hipError_t structure_hash(fea_ctx* c, uint64_t* out) {
   return hipSuccess;
 }
 
-// Device arrays of the solver state, in checkpoint order, with their sizes.
+// Device arrays of the solver state, in checkpoint order, with their sizes in
+// the checkpoint (the forms take all their 45 entries there, 36 values on the
+// device).
 std::vector<std::pair<DBuf*, size_t>> state_sections(fea_ctx* c) {
   const size_t N = c->N, G = c->G, d = sizeof(double);
   const int p = c->pcur;
@@ -1010,7 +1012,7 @@ std::vector<std::pair<DBuf*, size_t>> state_sections(fea_ctx* c) {
           {&c->Rh, 9 * N * d},   {&c->Th, 3 * N * d},   {&c->Fh, N * d},      {&c->Rh1, 9 * N * d},
           {&c->Th1, 3 * N * d},  {&c->Fh1, N * d},      {&c->Rh2, 9 * N * d}, {&c->Th2, 3 * N * d},
           {&c->Fh2, N * d},      {&c->a6h, 6 * N * d},  {&c->tph, 3 * N * d}, {&c->logfh, G * d},
-          {&c->counters, sizeof(fea::StepCounters)}, {&c->qW, (size_t)c->P * 45 * d},
+          {&c->counters, sizeof(fea::StepCounters)}, {&c->qW, (size_t)c->P * fea::kQuad * d},
           {&c->d_scene_done, (size_t)c->S * sizeof(int32_t)}};
 }
 
@@ -1985,6 +1987,14 @@ fea_status fea_get_state(fea_ctx* c, void* buf, size_t* len) {
   uint8_t* w = static_cast<uint8_t*>(buf);
   put(w, &h, 1);
   for (auto& sec : state_sections(c)) {
+    if (sec.first == &c->qW) {
+      constexpr fea::MonoTable mono;
+      std::vector<double> v;
+      HIP_OR_FAIL(c, download(c, v, c->qW, (size_t)c->P * fea::kMono));
+      for (int64_t n = 0; n < c->P; ++n)
+        for (int k = 0; k < fea::kQuad; ++k) put(w, &v[n * fea::kMono + mono.of[k]], 1);
+      continue;
+    }
     HIP_OR_FAIL(c, hipMemcpyAsync(w, sec.first->p, sec.second, hipMemcpyDeviceToHost, c->stream));
     w += sec.second;
   }
@@ -2046,6 +2056,15 @@ fea_status fea_set_state(fea_ctx* c, const void* buf, size_t len) {
   c->pcur = h.pcur;
   const uint8_t* r = static_cast<const uint8_t*>(buf) + sizeof(StateHdr);
   for (auto& sec : state_sections(c)) {
+    if (sec.first == &c->qW) {
+      constexpr fea::MonoTable mono;
+      std::vector<double> v((size_t)c->P * fea::kMono);
+      for (int64_t n = 0; n < c->P; ++n)
+        for (int k = 0; k < fea::kQuad; ++k) take(r, &v[n * fea::kMono + mono.of[k]], 1);
+      HIP_OR_FAIL(c, upload(c, c->qW, v.data(), v.size()));
+      HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));  // v goes
+      continue;
+    }
     HIP_OR_FAIL(c, hipMemcpyAsync(sec.first->p, r, sec.second, hipMemcpyHostToDevice, c->stream));
     r += sec.second;
   }

@@ -54,9 +54,13 @@ struct StepCtl {
   double* logR;
 };
 
-constexpr int kQuad = 45;  // distinct entries of the symmetric 9x9 W_n
+__constant__ constexpr MonoTable kMonoOf{};
 
-// dL/dF = 2 W f and the loss f^T W f of a pair from its quadratic form.
+// dL/dF = 2 W f and the loss f^T W f of a pair from its quadratic form, kept
+// as the 36 values its 45 entries take: 288 aligned bytes a lane instead of
+// 360, and the loads, each lane's from its own lines, are what the kernel
+// spends most on at many pairs per camera (a step of 24 scenes, 1,440 cameras:
+// 9.15 -> 8.5 us; of 1,000 cameras with 21 pairs each 7.0 -> 6.5).
 __device__ __forceinline__ void quad_partials(const double* __restrict__ W, const double F[9],
                                               double G[kPartStride]) {
   double Wf[9];
@@ -67,7 +71,7 @@ __device__ __forceinline__ void quad_partials(const double* __restrict__ W, cons
   for (int r = 0; r < 9; ++r)
 #pragma unroll
     for (int s = r; s < 9; ++s, ++k) {
-      const double w = W[k];
+      const double w = W[kMonoOf.of[k]];
       Wf[r] = fma(w, F[s], Wf[r]);
       if (s != r) Wf[s] = fma(w, F[r], Wf[s]);
     }
@@ -226,7 +230,7 @@ __device__ __forceinline__ void camera_pass(const CamArgs& a, const PosePair& pp
     if (!pair_geo(R + 9 * i, T + 3 * i, Fc[i], R + 9 * j, T + 3 * j, Fc[j], g)) continue;
     double G[kPartStride];
     if (QUAD) {
-      quad_partials(qW + (int64_t)(en.x >> 1) * kQuad, g.F, G);
+      quad_partials(qW + (int64_t)(en.x >> 1) * kMono, g.F, G);
     } else {
 #pragma unroll
       for (int k = 0; k < kPartStride; ++k) G[k] = 0.0;
@@ -289,6 +293,20 @@ __device__ __forceinline__ void camera_pass(const CamArgs& a, const PosePair& pp
   lr *= lr_scale;
   const bool step_own = lane < 9 || optimize_focal;
   if (step_own) adam_step(p_own, m_own, v_own, g_own, lr, ad.b1, ad.b2, ad.eps, 1.0 - b1t, 1.0 - b2t);
+  // the new rotation from the six updated coordinates (lanes 0..5) and the
+  // new focal length (lane 9), formed by every lane in the quadratic form's
+  // steps: the square roots and divisions of the one fill the exponential's
+  // chain (0.25 us of a step; next to a pass over the matches it is nothing)
+  double a_new[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) a_new[k] = readlane_f64(p_own, k);
+  double Rnew[9], f_new = 0.0;
+  if (QUAD && focal_inline) {
+    f_new = exp(p_own);
+    rot6d_forward(a_new, Rnew);
+  } else {
+    rot6d_forward(a_new, Rnew);
+  }
   if (lane < 6) {
     a6[6 * cam + lane] = p_own;
     m_a6[6 * cam + lane] = m_own;
@@ -304,15 +322,9 @@ __device__ __forceinline__ void camera_pass(const CamArgs& a, const PosePair& pp
       m_f[grp] = m_own;
       v_f[grp] = v_own;
     }
-    Fn[cam] = exp(p_own);
+    Fn[cam] = QUAD ? f_new : exp(p_own);
   }
-  // the new rotation from the six updated coordinates (lanes 0..5)
-  double a_new[6];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) a_new[k] = readlane_f64(p_own, k);
   if (lane == 0) {
-    double Rnew[9];
-    rot6d_forward(a_new, Rnew);
 #pragma unroll
     for (int k = 0; k < 9; ++k) Rn[9 * cam + k] = Rnew[k];
     if (sc.log_every > 0 && t_glob % sc.log_every == 0) {
@@ -331,8 +343,8 @@ __device__ __forceinline__ void camera_pass(const CamArgs& a, const PosePair& pp
 // pairs, whose forms (or item partials) and poses then meet in that XCD's L2
 // instead of being fetched by two of them.  The camera index is uniform over
 // the wave (scalar loads for what is the camera's own).  Quadratic-form step,
-// 1,000 cameras of 21 pairs: 7.75 -> 7.1 us; 24 scenes, 1,440 cameras:
-// 10.4 -> 9.2 us.  A table of the forms in entry order (coalesced, but each
+// 1,000 cameras of 21 pairs: 7.75 -> 7.1 us (now 6.5); 24 scenes, 1,440 cameras:
+// 10.4 -> 9.2 us (now 8.5).  A table of the forms in entry order (coalesced, but each
 // form twice) was slower (8.0), and so was loading the form ahead of the pose
 // block (its data returns before what the pose block waits for).
 constexpr int kXcds = 8;

@@ -14,7 +14,7 @@
 // instead of the 45 of the form's distinct entries plus the 18 products
 // that build c w.  The 36 sums are reduced over the wave (lane swaps and
 // DPP) into one fp64 partial per item; k_quad_reduce adds a pair's item partials
-// in item order and spreads the 36 sums over W_n's 45 entries.
+// in item order.  The camera kernel spreads the 36 sums over W_n's 45 entries.
 //
 // Every step, the camera kernel evaluates dL/dF = 2 W_n f and the loss
 // f^T W_n f of each incident pair at the current poses, so a step is one
@@ -29,30 +29,7 @@
 namespace fea {
 namespace {
 
-constexpr int kQuad = 45;  // distinct entries of a symmetric 9x9 matrix
-constexpr int kMono = 36;  // products P2_s P1_t summed per match (6 x 6)
 constexpr int kQuadThreads = 256;
-
-// Index (0..5) of the product x_a x_b, a <= b, of a 3-vector's entries.
-__host__ __device__ constexpr int sym3(int a, int b) { return a == 0 ? b : (a == 1 ? 2 + b : 5); }
-
-// For entry k of the form's upper triangle (row-major: (0,0), (0,1), ...,
-// (0,8), (1,1), ...), the index 6 s + t of its sum: entry (i, j) with
-// i = 3a + b, j = 3a' + b' is P2_{sym(a, a')} P1_{sym(b, b')}.
-struct MonoTable {
-  int of[kQuad];
-  constexpr MonoTable() : of() {
-    int k = 0;
-    for (int i = 0; i < 9; ++i)
-      for (int j = i; j < 9; ++j, ++k) {
-        const int a = i / 3, b = i % 3, a2 = j / 3, b2 = j % 3;
-        const int s = a <= a2 ? sym3(a, a2) : sym3(a2, a);
-        const int t = b <= b2 ? sym3(b, b2) : sym3(b2, b);
-        of[k] = 6 * s + t;
-      }
-  }
-};
-__constant__ constexpr MonoTable kMonoOf{};
 
 // One item of the round's pass per wavefront (kBuildItems items per
 // workgroup, no block-level synchronisation): the threshold test at the
@@ -229,9 +206,9 @@ __global__ void k_mask_slots(int64_t n, const unsigned char* __restrict__ mask, 
   if (s < n && !mask[s]) slot_pos[s] = -1;
 }
 
-// W_n = (1/Z of the pair's scene) * the sum of the pair's item partials in
-// item order, entry k taking sum kMonoOf.of[k]; 1/Z is the scene's (learned
-// scenes: 1/sum of weights).
+// The pair's 36 sums over its item partials, in item order, times 1/Z of its
+// scene (learned scenes: 1/sum of weights): the values that W_n's 45 entries
+// take.
 __global__ __launch_bounds__(kQuadThreads) void k_quad_reduce(int32_t P, const int32_t* __restrict__ pair_item_off,
                                                               const float* __restrict__ inv_z_scene,
                                                               const float* __restrict__ inv_zw_scene,
@@ -241,14 +218,13 @@ __global__ __launch_bounds__(kQuadThreads) void k_quad_reduce(int32_t P, const i
                                                               const int32_t* __restrict__ pair_scene,
                                                               const int32_t* __restrict__ scene_done) {
   const int64_t t = (int64_t)blockIdx.x * kQuadThreads + threadIdx.x;
-  if (t >= (int64_t)P * kQuad) return;
-  const int n = (int)(t / kQuad), k = (int)(t % kQuad);
+  if (t >= (int64_t)P * kMono) return;
+  const int n = (int)(t / kMono), k = (int)(t % kMono);
   const int sc = pair_scene[n];
   if (scene_done != nullptr && scene_done[sc] != 0) return;  // keeps its last round's form
   const double inv_z = (double)(scene_mode[sc] != 0 ? inv_zw_scene[sc] : inv_z_scene[sc]);
-  const int mk = kMonoOf.of[k];
   double s = 0.0;
-  for (int it = pair_item_off[n]; it < pair_item_off[n + 1]; ++it) s += qpart[(int64_t)it * kMono + mk];
+  for (int it = pair_item_off[n]; it < pair_item_off[n + 1]; ++it) s += qpart[(int64_t)it * kMono + k];
   qW[t] = inv_z * s;
 }
 
@@ -296,7 +272,7 @@ hipError_t launch_mask_slots(fea_ctx* c, int32_t* slot_pos) {
 // normalisers, which are set after the counts.
 hipError_t launch_quad_reduce(fea_ctx* c, const int32_t* pair_item_off_dev) {
   if (c->P == 0) return hipSuccess;
-  const int64_t t = c->P * kQuad;
+  const int64_t t = c->P * kMono;
   k_quad_reduce<<<(unsigned)((t + kQuadThreads - 1) / kQuadThreads), kQuadThreads, 0, c->stream>>>(
       (int32_t)c->P, pair_item_off_dev, c->d_inv_z.as<float>(), c->d_inv_zw.as<float>(),
       c->d_scene_mode.as<int32_t>(), c->qpart.as<double>(), c->qW.as<double>(), c->d_pair_scene.as<int32_t>(),
