@@ -1419,6 +1419,11 @@ fea_status put_poses(fea_ctx* c, const double* R, const double* t, const double*
     for (int k = 0; k < 3; ++k)
       tt[3 * i + k] = -(Rc[9 * i + 3 * k] * on[0] + Rc[9 * i + 3 * k + 1] * on[1] + Rc[9 * i + 3 * k + 2] * on[2]);
   }
+  // a captured launch would read the ring when it is replayed, not now
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  HIP_OR_FAIL(c, hipStreamIsCapturing(c->stream, &capturing));
+  if (capturing != hipStreamCaptureStatusNone)
+    return fail(c, FEA_EDEVICE, "poses cannot be set while their stream is being captured");
   // through the pinned ring, which holds them at any number of cameras; no
   // wait, as the ring keeps them until the stream has passed
   static_assert((size_t)20 * 65535 * sizeof(double) <= kStageBytes, "poses of 65,535 cameras and as many groups");
