@@ -69,11 +69,11 @@ BATCH_CONVERGE_DEG = 0.01
 KERNEL_SOURCES = ("paper_2605_18052_amd/csrc/fea_resgrad.hip", "paper_2605_18052_amd/csrc/fea_device.h",
                   "paper_2605_18052_amd/csrc/fea_layout.h")
 PMC_TRAFFIC = {
-    "sources_sha256": "0da24db5ded85a54879b5459a4eb845c5d1291db8ce787a3be8fa4edbe0aa79d",
+    "sources_sha256": "b6ec73f6635b4c1701498eba2cb6574b968f139c4b53fc8d0baa75d0e2f1ca4a",
     # retained matches per launch -> "matches x threads" -> fetched + written bytes
     "bytes_per_launch": {
         87275962: {  # traj3000_m100M, round 0
-            "2048x256": 1448063047, "1024x256": 1484844646,
+            "2048x256": 1448058443, "1024x256": 1484845126,
         },
     },
 }
