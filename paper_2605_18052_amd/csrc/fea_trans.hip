@@ -25,6 +25,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -762,14 +763,22 @@ hipError_t launch_rt_score_t(hipStream_t st, int64_t n_items, int n_groups, cons
                              const float* x1, const float* y1, const float* x2, const float* y2, const float* cand,
                              int n_cand, int kp, float tau, float* partial, float* item_abs, hipEvent_t ev0,
                              hipEvent_t ev1) {
-  const dim3 grid((unsigned)(n_items * n_groups)), block(kRtThreads);
-  if (ev0)
-    hipExtLaunchKernelGGL(k_rt_score<CAP>, grid, block, 0, st, ev0, ev1, 0, items, n_groups, rowf, x1, y1, x2, y2,
-                          cand, n_cand, kp, tau, partial, item_abs);
-  else
-    k_rt_score<CAP><<<grid, block, 0, st>>>(items, n_groups, rowf, x1, y1, x2, y2, cand, n_cand, kp, tau, partial,
-                                            item_abs);
-  return hipGetLastError();
+  const dim3 block(kRtThreads);
+  const int64_t most = grid_rows(n_groups, kRtThreads);  // items a launch takes
+  hipError_t e = hipSuccess;
+  for (int64_t i = 0; i < n_items && e == hipSuccess; i += most) {
+    const int64_t n = std::min(most, n_items - i);
+    const dim3 grid((unsigned)(n * n_groups));
+    if (ev0)
+      hipExtLaunchKernelGGL(k_rt_score<CAP>, grid, block, 0, st, i == 0 ? ev0 : nullptr,
+                            i + n == n_items ? ev1 : nullptr, 0, items + i, n_groups, rowf, x1, y1, x2, y2, cand, n_cand,
+                            kp, tau, partial + i * kp, item_abs + i);
+    else
+      k_rt_score<CAP><<<grid, block, 0, st>>>(items + i, n_groups, rowf, x1, y1, x2, y2, cand, n_cand, kp, tau,
+                                              partial + i * kp, item_abs + i);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 hipError_t launch_rt_score(hipStream_t st, int64_t n_items, int n_groups, const int4* items, const float* rowf,
