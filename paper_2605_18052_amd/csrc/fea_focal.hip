@@ -21,6 +21,7 @@
 #include <cstdint>
 
 #include "fea_focal.h"
+#include "fea_grid.h"
 
 namespace fea {
 namespace {
@@ -333,18 +334,29 @@ hipError_t launch_fv_vote(hipStream_t st, int n_groups, int n_items, int64_t n_e
       n_entries, ent_group, ent_pair, pair_i, pair_j, group, F, f_cur, f0, fe);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t waves = n_items * nb;
-  const dim3 grid((unsigned)((waves + kFvThreads / 64 - 1) / (kFvThreads / 64))), block(kFvThreads);
   double* out = n_items == n_groups ? votes : partial;
   const double inv_f0 = f0 > 0.0 ? 1.0 / f0 : 1.0;
-  if (ev0)
-    hipExtLaunchKernelGGL(k_fv_vote, grid, block, 0, st, ev0, ev1, 0, n_items, n_cand, items, fe, cand, 1.0 / tau,
-                          inv_f0, out);
-  else
-    k_fv_vote<<<grid, block, 0, st>>>(n_items, n_cand, items, fe, cand, 1.0 / tau, inv_f0, out);
-  if ((e = hipGetLastError()) != hipSuccess || n_items == n_groups) return e;
-  k_fv_sum<<<(unsigned)(n_groups * nb), 64 * kFvSumWaves, 0, st>>>(n_cand, grp_item_off, partial, votes);
-  return hipGetLastError();
+  // slices of the items, and of the groups below, that a grid holds
+  constexpr int kWaves = kFvThreads / 64;
+  const int64_t most = std::max<int64_t>(grid_rows(1, kFvThreads) * kWaves / nb, 1);
+  for (int64_t i = 0; i < n_items; i += most) {
+    const int n = (int)std::min<int64_t>(most, n_items - i);
+    const dim3 grid((unsigned)((n * nb + kWaves - 1) / kWaves)), block(kFvThreads);
+    if (ev0)
+      hipExtLaunchKernelGGL(k_fv_vote, grid, block, 0, st, i == 0 ? ev0 : nullptr, i + n == n_items ? ev1 : nullptr, 0,
+                            n, n_cand, items + i, fe, cand, 1.0 / tau, inv_f0, out + i * n_cand);
+    else
+      k_fv_vote<<<grid, block, 0, st>>>(n, n_cand, items + i, fe, cand, 1.0 / tau, inv_f0, out + i * n_cand);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (n_items == n_groups) return e;
+  const int64_t most_groups = grid_rows(nb, 64 * kFvSumWaves);
+  for (int64_t g = 0; g < n_groups && e == hipSuccess; g += most_groups) {
+    const int64_t n = std::min<int64_t>(most_groups, n_groups - g);
+    k_fv_sum<<<(unsigned)(n * nb), 64 * kFvSumWaves, 0, st>>>(n_cand, grp_item_off + g, partial, votes + g * n_cand);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 hipError_t launch_fv_best(hipStream_t st, int n_groups, int n_cand, const double* votes, const double* cand,

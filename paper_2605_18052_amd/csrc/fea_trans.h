@@ -19,14 +19,6 @@ constexpr int kRtBlocks = 4;
 constexpr int kRtGroup = 4 * kRtBlocks * 32;
 constexpr int kRtRow = 16;  // per-pair row: R_ij (9), 1/f_i, 1/f_j, cx_i, cy_i, cx_j, cy_j, pad
 
-// Rows that one launch takes in grid.x when a row is `blocks` workgroups of
-// `threads`: a dispatch counts its threads in 32 bits, and a launch of 2^32 or
-// more is refused or, silently, runs only its low 32 bits' worth.
-constexpr int64_t grid_rows(int64_t blocks, int threads) {
-  const int64_t rows = ((int64_t(1) << 32) - 1) / threads / blocks;
-  return rows > 1 ? rows : 1;
-}
-
 // Adam state shared by all cameras of one alignment phase, one slot per step
 // parity: the learning rate of the step and the running powers of the betas.
 struct TaCounters {

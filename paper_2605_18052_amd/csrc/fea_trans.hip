@@ -30,6 +30,7 @@
 #include <cstdint>
 
 #include "fea_device.h"
+#include "fea_grid.h"
 #include "fea_trans.h"
 
 namespace fea {

@@ -59,3 +59,34 @@ def test_search_over_more_candidates_and_items_than_one_launch_takes():
         tol = 1e-6 + 1e-5 * lo  # of fp32 scores, as in gpu_helpers.score_tol
         assert abs(got["score_best"][p] - lo) <= tol
         assert float(ref[int(got["best"][p])]) <= lo + 2 * tol
+
+
+def test_vote_over_more_groups_and_candidates_than_one_launch_takes():
+    """16,384 groups by 16,384 candidates with one group's pairs cut into runs:
+    4.2 million blocks of 64 candidates, whose sums take 1,024 threads each."""
+    G, K, shared = 16384, 16384, 40
+    rng = np.random.default_rng(1)
+    n = G - 1 + shared
+    grp = np.concatenate([np.zeros(shared, np.int32), np.arange(1, G, dtype=np.int32)])
+    a, b = np.triu_indices(shared, 1)
+    far = np.arange(n - 50, n)  # 25 pairs among the last groups
+    pc = np.concatenate([np.stack([a, b], 1), far.reshape(25, 2)]).astype(np.int32)
+    F = rng.normal(size=(len(pc), 3, 3))
+    U, _, Vt = np.linalg.svd(F)
+    F = (U * np.stack([1 + rng.uniform(0, 0.5, len(F)), np.ones(len(F)), np.zeros(len(F))], 1)[:, None, :]) @ Vt
+    d = np.array([1 / 700.0, 1 / 700.0, 1.0])
+    F = d[:, None] * F * d
+    cand = synth.focal_candidates(K, 200.0, 3000.0)
+    fcur = rng.uniform(400, 1200, G)
+    with fastea.Context(0) as ctx:
+        got = ctx.focal_vote(n, pc, F, cand, 0.05, group=grp, f_cur=fcur)
+        # the same votes in calls of few groups
+        one = ctx.focal_vote(shared, pc[:len(a)], F[:len(a)], cand, 0.05, votes=True)
+        last = ctx.focal_vote(50, far.reshape(25, 2) - (n - 50), F[len(a):], cand, 0.05,
+                              group=np.arange(50, dtype=np.int32), f_cur=fcur[G - 50:], votes=True)
+    # the runs are cut elsewhere: the sums agree to rounding, the choice to a tie of it
+    v = one["votes"][0]
+    assert v[got["k_best"][0]] >= v.max() * (1 - 1e-12)
+    np.testing.assert_array_equal(got["k_best"][G - 50:], last["k_best"])
+    np.testing.assert_array_equal(got["k_best"][1:G - 50], 0)  # no pairs: every vote zero, the first candidate
+    np.testing.assert_array_equal(got["f_best"], cand[got["k_best"]])
