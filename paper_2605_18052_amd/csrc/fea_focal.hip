@@ -126,10 +126,15 @@ __global__ __launch_bounds__(kFvThreads) void k_fv_entries(int64_t n_entries, co
   r.cand_i = ci;
   r.cand_j = cj;
   r.pad = 0;
+  // F may come at any scale; brought near 1 by a power of two, which changes no
+  // bit of a ratio (the cubic's products go to the sixth order in F)
+  double top = 0.0;
+  for (int k = 0; k < 9; ++k) top = fmax(top, fabs(F[9 * (int64_t)p + k]));
+  const int ex = top > 0.0 ? -ilogb(top) : 0;
   double E[9];  // columns of E0 (of its transpose when only side j takes the candidate), at f0
   for (int k = 0; k < 3; ++k)
     for (int c = 0; c < 3; ++c) {
-      const double x = sj[k] * F[9 * (int64_t)p + 3 * k + c] * si[c];
+      const double x = sj[k] * ldexp(F[9 * (int64_t)p + 3 * k + c], ex) * si[c];
       r.v[3 * k + c] = x;
       const double y = x * (cj && k < 2 ? f0 : 1.0) * (ci && c < 2 ? f0 : 1.0);
       E[ci ? 3 * c + k : 3 * k + c] = y;
