@@ -38,8 +38,14 @@ constexpr int64_t kFvMinRun = 8;
 // For any rank: s1 / s2 of a 3x3 matrix from the eigenvalues e1 >= e2 >= e3 of M = E^T E:
 // with q = tr(M)/3 and p^2 = |M - qI|_F^2 / 6, the eigenvalues of
 // B = (M - qI)/p are 2 cos(phi + 2 pi k/3) with cos(3 phi) = det(B)/2.
-// Infinite when s2 = 0 (rank below 2).
-__device__ __noinline__ double sv_ratio_full(const double* E) {
+// Infinite when s2 = 0 (rank below 2).  A function of its own, so that the
+// rank-2 forms keep 65 registers and 7 waves per SIMD (inlined: 98 and 4, and
+// 72 -> 85 us for the votes of 1,000 cameras), its matrix passed in registers
+// (through private memory 408 us for full-rank matrices, now 278; a kernel of
+// the cubic alone 290).
+__device__ __noinline__ double sv_ratio_full(double x0, double x1, double x2, double x3, double x4, double x5,
+                                             double x6, double x7, double x8) {
+  const double E[9] = {x0, x1, x2, x3, x4, x5, x6, x7, x8};
   const double m00 = E[0] * E[0] + E[3] * E[3] + E[6] * E[6];
   const double m11 = E[1] * E[1] + E[4] * E[4] + E[7] * E[7];
   const double m22 = E[2] * E[2] + E[5] * E[5] + E[8] * E[8];
@@ -79,7 +85,8 @@ __device__ __noinline__ double sv_ratio_full(const double* E) {
 // s1/s2 = (S00 + S11 + d) / (2 sqrt(det S)).  Nothing small is formed from
 // large terms that nearly cancel: s1/s2 - 1 comes out to ~1e-15, where the
 // cubic's closed form fixes it to ~1e-8 near s1 = s2.  A matrix of full
-// rank, or scaled beyond what these products carry, keeps the cubic.
+// rank, or with focal lengths beyond what these products carry, keeps the
+// cubic.
 enum : int { kFvOneSide = 0, kFvBothSides = 1, kFvFull = 2 };
 
 struct FvEntry {
@@ -253,9 +260,8 @@ __global__ __launch_bounds__(kFvThreads) void k_fv_vote(int n_items, int n_cand,
       ratio = 0.5 * (a + c + d) * fast_rsqrt(dg * dh * g00 * g00);
     } else {
       const double fi = r.cand_i ? f : 1.0, fj = r.cand_j ? f : 1.0;
-      const double E[9] = {v[0] * fj * fi, v[1] * fj * fi, v[2] * fj, v[3] * fj * fi, v[4] * fj * fi,
-                           v[5] * fj,      v[6] * fi,      v[7] * fi, v[8]};
-      ratio = sv_ratio_full(E);
+      ratio = sv_ratio_full(v[0] * fj * fi, v[1] * fj * fi, v[2] * fj, v[3] * fj * fi, v[4] * fj * fi, v[5] * fj,
+                            v[6] * fi, v[7] * fi, v[8]);
     }
     s += exp((1.0 - ratio) * inv_tau);
   }
