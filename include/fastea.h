@@ -273,14 +273,18 @@ fea_status fea_load_matches_device(fea_ctx *ctx, int64_t n, const float *x1_dev,
  * earlier stages and optimises world-to-camera poses): R [n_cams*9]
  * row-major world-to-camera rotations, t [n_cams*3]; host arrays.  Rotations must be proper (det > 0) and finite.
  * Applies the gauge normalisation if enabled and resets the round state.
- * FEA_EDEGENERATE if two matched cameras share a centre. */
+ * FEA_EDEGENERATE if two matched cameras share a centre; FEA_EDEVICE, with the
+ * solver as it was, while the context's stream is being captured. */
 fea_status fea_init_poses(fea_ctx *ctx, const double *R, const double *t);
 
 /* Replaces the current poses (caller's frame, host arrays: R [n_cams*9],
  * t [n_cams*3], f [n_cams] or NULL to keep the focal lengths) without
  * touching the round: the snapshot, the retained matches and the Adam moments
  * stay as they are.  Used to evaluate the objective at arbitrary poses and by
- * optimisers that run outside the library.  Requires fea_init_poses. */
+ * optimisers that run outside the library.  Requires fea_init_poses;
+ * FEA_EDEVICE while the context's stream is being captured.  The arrays are
+ * the caller's again when the call returns; the poses are set in stream order,
+ * without a wait. */
 fea_status fea_set_poses(fea_ctx *ctx, const double *R, const double *t, const double *f);
 
 /* Starts an IRLS round (re-weighting rounds and outlier filtering of the

@@ -1348,6 +1348,16 @@ fea_status fea_load_matches_device(fea_ctx* c, int64_t n, const float* x1, const
 
 namespace {
 
+// Poses are read from the staging ring by a launch: a captured one would read
+// it when it is replayed.
+fea_status refuse_capture(fea_ctx* c) {
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  HIP_OR_FAIL(c, hipStreamIsCapturing(c->stream, &capturing));
+  if (capturing != hipStreamCaptureStatusNone)
+    return fail(c, FEA_EDEVICE, "poses cannot be set while their stream is being captured");
+  return FEA_OK;
+}
+
 // Validates caller-frame poses, writes the 6D parameters, the derived R/t
 // (internal gauge) and, if f is given, log f per group and f per camera.
 // With set_gauge the gauge (centre, scale) is recomputed from these poses.
@@ -1419,11 +1429,6 @@ fea_status put_poses(fea_ctx* c, const double* R, const double* t, const double*
     for (int k = 0; k < 3; ++k)
       tt[3 * i + k] = -(Rc[9 * i + 3 * k] * on[0] + Rc[9 * i + 3 * k + 1] * on[1] + Rc[9 * i + 3 * k + 2] * on[2]);
   }
-  // a captured launch would read the ring when it is replayed, not now
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  HIP_OR_FAIL(c, hipStreamIsCapturing(c->stream, &capturing));
-  if (capturing != hipStreamCaptureStatusNone)
-    return fail(c, FEA_EDEVICE, "poses cannot be set while their stream is being captured");
   // through the pinned ring, which holds them at any number of cameras; no
   // wait, as the ring keeps them until the stream has passed
   static_assert((size_t)20 * 65535 * sizeof(double) <= kStageBytes, "poses of 65,535 cameras and as many groups");
@@ -1455,9 +1460,11 @@ fea_status fea_init_poses(fea_ctx* c, const double* R, const double* t) {
   if (!c->have_matches) return fail(c, FEA_ESTATE, "load matches first");
   if (!R || !t) return fail(c, FEA_EINVAL, "R and t are required");
   DeviceGuard g(c->device);
+  fea_status s = refuse_capture(c);  // before anything of the solver changes
+  if (s != FEA_OK) return s;
   c->have_poses = false;
   c->pcur = 0;
-  fea_status s = put_poses(c, R, t, c->f_in.data(), true);
+  s = put_poses(c, R, t, c->f_in.data(), true);
   if (s != FEA_OK) return s;
   HIP_OR_FAIL(c, reset_layout(c));
   // the per-camera loss shares are read by the non-finite guard before any
@@ -1482,7 +1489,8 @@ fea_status fea_set_poses(fea_ctx* c, const double* R, const double* t, const dou
   if (!c->have_poses) return fail(c, FEA_ESTATE, "initialise poses first");
   if (!R || !t) return fail(c, FEA_EINVAL, "R and t are required");
   DeviceGuard g(c->device);
-  return put_poses(c, R, t, f, false);
+  const fea_status s = refuse_capture(c);
+  return s == FEA_OK ? put_poses(c, R, t, f, false) : s;
 }
 
 fea_status fea_begin_round(fea_ctx* c, double tau_px) {
