@@ -40,3 +40,10 @@ def test_vote_keeps_its_matrix_in_registers():
     """The cubic of a full-rank matrix is a function of its own; its nine
     entries go to it in registers."""
     assert _kernel(_report("fea_focal.hip"), "k_fv_vote")["ScratchSize"] == 0
+
+
+def test_per_match_camera_kernel_keeps_three_waves_per_simd():
+    """512 registers per SIMD lane in blocks of 8: at most 168 for a third
+    wave, without which 3,000 cameras take a second round."""
+    r = _kernel(_report("fea_camera.hip"), "k_camgradILb0")
+    assert r["VGPRs"] <= 168 and r["ScratchSize"] == 0
