@@ -2664,6 +2664,9 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
   }
   const int64_t P = c->P;
   if (P == 0) return FEA_OK;
+  int64_t longest = 0;
+  for (int64_t n = 0; n < P; ++n) longest = std::max(longest, c->seg_off[n + 1] - c->seg_off[n]);
+  const bool split = fea::rt_split(P, c->M, longest, n_cand, tau);
   // work items over the full layout (each pair's run aligned as when loaded)
   std::vector<int4> items;
   std::vector<int32_t> pio((size_t)P + 1);
@@ -2671,9 +2674,10 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
   for (int64_t n = 0; n < P; ++n) {
     const int64_t cnt = c->seg_off[n + 1] - c->seg_off[n];
     pio[n] = (int32_t)items.size();
-    // equal runs of at most kRtItem, whole blocks of 32 matches but the last
+    // split products: equal runs of at most kRtItem, whole blocks of 32 matches
+    // but the last
     const int64_t runs = (cnt + fea::kRtItem - 1) / fea::kRtItem;
-    const int64_t len = runs > 0 ? ((cnt + runs - 1) / runs + 31) / 32 * 32 : 0;
+    const int64_t len = split && runs > 0 ? ((cnt + runs - 1) / runs + 31) / 32 * 32 : fea::kRtItem;
     for (int64_t s = 0; s < cnt; s += len) {
       if (off + s > INT32_MAX) return fail(c, FEA_EINVAL, "layout too large for the candidate search");
       items.push_back(make_int4((int)n, (int)(off + s), (int)std::min<int64_t>(len, cnt - s), 0));
@@ -2682,8 +2686,9 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
   }
   pio[P] = (int32_t)items.size();
   const int64_t n_items = (int64_t)items.size();
-  const int groups = (n_cand + fea::kRtGroup - 1) / fea::kRtGroup;
-  const int kp = groups * fea::kRtGroup;
+  const int group = split ? fea::kRtGroup : fea::kRtGroup32;
+  const int groups = (n_cand + group - 1) / group;
+  const int kp = groups * group;
   std::vector<float> cs((size_t)3 * kp, 0.f);  // structure of arrays, zero-padded
   for (int32_t k = 0; k < n_cand; ++k)
     for (int a = 0; a < 3; ++a) cs[(size_t)a * kp + k] = (float)cand[3 * (size_t)k + a];
@@ -2718,10 +2723,10 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
     HIP_OR_FAIL(c, hipEventCreate(&ev[0]));
     HIP_OR_FAIL(c, hipEventCreate(&ev[1]));
   }
-  hipError_t e = fea::launch_rt_score(c->stream, n_items, groups, ditems, rowf, x1, y1, x2, y2, dcand, n_cand, kp,
+  hipError_t e = fea::launch_rt_score(c->stream, split, n_items, groups, ditems, rowf, x1, y1, x2, y2, dcand, n_cand, kp,
                                       tau, part, iabs, ev[0], ev[1]);
   if (e == hipSuccess)
-    e = fea::launch_rt_select(c->stream, P, n_cand, kp, tau, dpio, ditems, part, iabs, dcand, rowf, rowd, x1, y1, x2,
+    e = fea::launch_rt_select(c->stream, split, P, n_cand, kp, tau, dpio, ditems, part, iabs, dcand, rowf, rowd, x1, y1, x2,
                               y2, dscores, dbest, dvote, dt, dsb);
   if (e == hipSuccess) e = sc.get(t_rel, dt, (size_t)3 * P);
   if (e == hipSuccess) e = sc.get(best, dbest, (size_t)P);

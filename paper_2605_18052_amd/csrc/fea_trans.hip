@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <tuple>
 
 #include "fea_device.h"
 #include "fea_grid.h"
@@ -45,6 +46,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRtThreads = 256;
 constexpr int kRtLds = kRtItem + 32;              // LDS row stride (floats): a block past the last is readable
+constexpr int kRtLds32 = kRtItem + 16;            // the same of fp32 products; rows land 16 banks apart
 constexpr int kTaThreads = 256;
 
 // ---- relative translations ---------------------------------------------------
@@ -250,6 +252,92 @@ __global__ __launch_bounds__(kRtThreads) void k_rt_score(const int4* __restrict_
   }
 }
 
+// Four products of one candidate, capped or not, added.
+__device__ __forceinline__ float rt_four(const f32x4 d, bool cap, float ntau, float tau) {
+  if (cap) {
+    const float c0 = __builtin_amdgcn_fmed3f(d[0], ntau, tau), c1 = __builtin_amdgcn_fmed3f(d[1], ntau, tau);
+    const float c2 = __builtin_amdgcn_fmed3f(d[2], ntau, tau), c3 = __builtin_amdgcn_fmed3f(d[3], ntau, tau);
+    return (__builtin_fabsf(c0) + __builtin_fabsf(c1)) + (__builtin_fabsf(c2) + __builtin_fabsf(c3));
+  }
+  return (__builtin_fabsf(d[0]) + __builtin_fabsf(d[1])) + (__builtin_fabsf(d[2]) + __builtin_fabsf(d[3]));
+}
+
+// The same with fp32 products, kRtGroup32 candidates over one work item, for
+// the calls that rt_split leaves to them.  MFMA 16x16x4: lane l supplies
+// component l/16 of match l%16 of the block (A) and of candidate l%16 (B),
+// component 3 zero, and receives candidate l%16 at four matches.  Sums of at
+// most 128 terms per lane in fp32, then at most 4 of those.
+template <bool CAP>
+__global__ __launch_bounds__(kRtThreads) void k_rt_score32(const int4* __restrict__ items, int n_groups,
+                                                           const float* __restrict__ rowf,
+                                                           const float* __restrict__ x1, const float* __restrict__ y1,
+                                                           const float* __restrict__ x2, const float* __restrict__ y2,
+                                                           const float* __restrict__ cand, int n_cand, int kp,
+                                                           float tau, float* __restrict__ partial) {
+  __shared__ float sn[3][kRtLds32];
+  const int it = blockIdx.x / n_groups;
+  const int grp = blockIdx.x - it * n_groups;
+  const int4 rec = items[it];  // {pair, layout start, count, -}
+  const int cnt = rec.z;
+  const int nblk = (cnt + 15) >> 4;
+  {
+    const RtPair pr(rowf + (int64_t)kRtRow * rec.x);
+    for (int m = threadIdx.x; m < (nblk << 4); m += kRtThreads) {
+      float n[3] = {0.f, 0.f, 0.f};
+      if (m < cnt) {
+        const int64_t s = (int64_t)rec.y + m;
+        pr.normal(x1[s], y1[s], x2[s], y2[s], n);
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) sn[k][m] = n[k];
+    }
+  }
+  __syncthreads();
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kq = lane >> 4, col = lane & 15;
+  const int cbase = grp * kRtGroup32 + wave * (kRtBlocks32 * 16);
+  if (cbase >= n_cand) return;  // the whole wave: nothing but padding
+  float bop[kRtBlocks32];
+#pragma unroll
+  for (int q = 0; q < kRtBlocks32; ++q) bop[q] = kq < 3 ? cand[(int64_t)kq * kp + cbase + 16 * q + col] : 0.f;
+  float accf[kRtBlocks32], acc2[kRtBlocks32];
+#pragma unroll
+  for (int q = 0; q < kRtBlocks32; ++q) {
+    accf[q] = 0.f;
+    acc2[q] = 0.f;
+  }
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const float ntau = -tau;
+  // the row of the next block is read while this one's products run (the
+  // read past the last block stays inside the LDS row)
+  const float* srow = sn[kq < 3 ? kq : 0];
+  float a_next = srow[col];
+  for (int mb = 0; mb < nblk; ++mb) {
+    const float a = kq < 3 ? a_next : 0.f;
+    a_next = srow[((mb + 1) << 4) + col];
+#pragma unroll
+    for (int q = 0; q < kRtBlocks32; ++q) {
+      const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bop[q], zero, 0, 0, 0);
+      accf[q] += rt_four(d, CAP, ntau, tau);
+    }
+    if ((mb & 31) == 31) {
+#pragma unroll
+      for (int q = 0; q < kRtBlocks32; ++q) {
+        acc2[q] += accf[q];
+        accf[q] = 0.f;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kRtBlocks32; ++q) {
+    double s = (double)acc2[q] + (double)accf[q];
+    s += __shfl_xor(s, 16);
+    s += __shfl_xor(s, 32);
+    if (kq == 0) partial[(int64_t)it * kp + cbase + 16 * q + col] = (float)s;
+  }
+}
+
 // Part of a candidate's (capped) sum over a run of matches with fp32
 // products, one candidate per column, by one wave: kRtSeg blocks of 16
 // matches from block mb0 on.  MFMA 16x16x4: lane l supplies component l/16
@@ -298,13 +386,7 @@ __device__ float rt_segment_sum(const RtPair& pr, int64_t start, int cnt, int mb
     for (int b = 0; b < 4; ++b) {
       const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b], u, zero, 0, 0, 0);
       if (mb + b >= nblk) break;  // uniform
-      if (cap) {
-        const float c0 = __builtin_amdgcn_fmed3f(d[0], ntau, tau), c1 = __builtin_amdgcn_fmed3f(d[1], ntau, tau);
-        const float c2 = __builtin_amdgcn_fmed3f(d[2], ntau, tau), c3 = __builtin_amdgcn_fmed3f(d[3], ntau, tau);
-        acc += (__builtin_fabsf(c0) + __builtin_fabsf(c1)) + (__builtin_fabsf(c2) + __builtin_fabsf(c3));
-      } else {
-        acc += (__builtin_fabsf(d[0]) + __builtin_fabsf(d[1])) + (__builtin_fabsf(d[2]) + __builtin_fabsf(d[3]));
-      }
+      acc += rt_four(d, cap, ntau, tau);
     }
   }
   return acc;
@@ -351,7 +433,10 @@ __device__ int cheirality_vote(const double* row, float fx1, float fy1, float fx
 // products throughout.  Anything not finite leaves every candidate in.
 // 10,600 pairs of 2,800 matches: 213 us with the vote alone, 367 us with the
 // second scoring.
+//
+// SPLIT false: the sums are those of fp32 products, and the lowest is taken.
 constexpr int kRtChunk = 1024;  // candidates looked through at a time
+template <bool SPLIT>
 __global__ __launch_bounds__(kRtThreads) void k_rt_select(int k_cand, int kp, double tau,
                                                           const int32_t* __restrict__ pair_item_off,
                                                           const int4* __restrict__ items,
@@ -367,13 +452,7 @@ __global__ __launch_bounds__(kRtThreads) void k_rt_select(int k_cand, int kp, do
                                                           double* __restrict__ score_best) {
   __shared__ double sv[kRtThreads];
   __shared__ int si[kRtThreads];
-  __shared__ int s_list[kRtChunk];      // contenders of the chunk
-  __shared__ double s_mean[kRtChunk];   // and their means in fp32 arithmetic
-  __shared__ int s_slot[kRtChunk];      // candidate of the chunk -> its place in the list, -1 when ruled out
-  __shared__ float s_seg[kRtWaves][64];
-  __shared__ float s_rows[kRtWaves][4][64];
-  __shared__ int s_n;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   const int64_t n = blockIdx.x;
   const int i0 = pair_item_off[n], i1 = pair_item_off[n + 1];
   const int64_t start = items[i0].y;  // the pair's items are one run of the layout
@@ -381,87 +460,105 @@ __global__ __launch_bounds__(kRtThreads) void k_rt_select(int k_cand, int kp, do
   double abs1 = 0.0;
   for (int it = i0; it < i1; ++it) {
     cnt += items[it].z;
-    abs1 += (double)item_abs[it];
+    if (SPLIT) abs1 += (double)item_abs[it];
   }
   auto mean_of = [&](int k) {
     double s = 0.0;
     for (int it = i0; it < i1; ++it) s += (double)partial[(int64_t)it * kp + k];
     return s / (double)cnt;
   };
-  double lo = INFINITY;
-  bool odd = false;
-  for (int k = tid; k < k_cand; k += kRtThreads) {
-    const double mean = mean_of(k);
-    if (scores) scores[n * k_cand + k] = (float)mean;
-    if (mean < lo) lo = mean;
-    odd = odd || !isfinite(mean);
-  }
-  sv[tid] = lo;
-  __syncthreads();
-  for (int s = kRtThreads / 2; s > 0; s >>= 1) {
-    if (tid < s && sv[tid + s] < sv[tid]) sv[tid] = sv[tid + s];
-    __syncthreads();
-  }
-  const double low = sv[0];
-  s_rows[wave][3][lane] = 0.f;
-  __syncthreads();
-  const double limit = low + 2.0 * 0x1p-24 * (70.0 * (abs1 / (double)cnt) + 200.0 * low);
-  const bool none = !odd && lo > limit;  // none of this thread's candidates remains
-  const RtPair pr(rowf + (int64_t)kRtRow * n);
-  const bool cap = !isinf(tau);
-  const float tauf = cap ? (float)tau : 0.f;
   double bv = 0.0;
   int bk = -1;
-  for (int c0 = 0; c0 < k_cand; c0 += kRtChunk) {
-    if (tid == 0) s_n = 0;
-    __syncthreads();
-    const int ce = min(c0 + kRtChunk, k_cand);
-    for (int k = c0 + tid; k < ce; k += kRtThreads) {
-      int slot = -1;
-      if (!none && !(mean_of(k) > limit)) {
-        slot = atomicAdd(&s_n, 1);
-        s_list[slot] = k;
-        s_mean[slot] = 0.0;
-      }
-      s_slot[k - c0] = slot;
-    }
-    __syncthreads();
-    const int nc = s_n;
-    for (int b = 0; b < nc; b += 16) {
-      // 16 contenders at a time over runs of kRtRun matches, a segment per
-      // wave: the full segments' lane sums are added in order, then the
-      // last, shorter one's and the lanes' in fp64
-      const int kq = lane >> 4, mine = b + (lane & 15);
-      const float u = kq < 3 && mine < nc ? cand[(int64_t)kq * kp + s_list[mine]] : 0.f;
-      for (int m0 = 0; m0 < cnt; m0 += kRtRun) {
-        const int rc = min(kRtRun, cnt - m0), nblk = (rc + 15) >> 4;
-        s_seg[wave][lane] =
-            rt_segment_sum(pr, start + m0, rc, wave * kRtSeg, u, cap, tauf, lane, s_rows[wave], x1, y1, x2, y2);
-        __syncthreads();
-        if (wave == 0) {
-          float acc2 = 0.f;
-          const int full = nblk / kRtSeg;
-          for (int w = 0; w < full; ++w) acc2 += s_seg[w][lane];
-          const float accf = full < kRtWaves ? s_seg[full][lane] : 0.f;
-          double s = (double)acc2 + (double)accf;
-          s += __shfl_xor(s, 16);
-          s += __shfl_xor(s, 32);
-          if (lane < 16 && mine < nc) s_mean[mine] += (double)(float)s;
-        }
-        __syncthreads();
-      }
-    }
-    for (int k = c0 + tid; k < ce; k += kRtThreads) {
-      const int slot = s_slot[k - c0];
-      if (slot < 0) continue;
-      const double mean = s_mean[slot] / (double)cnt;
+  if constexpr (!SPLIT) {
+    for (int k = tid; k < k_cand; k += kRtThreads) {
+      const double mean = mean_of(k);
       if (scores) scores[n * k_cand + k] = (float)mean;
       if (bk < 0 || mean < bv) {
         bv = mean;
         bk = k;
       }
     }
+  } else {
+    __shared__ int s_list[kRtChunk];      // contenders of the chunk
+    __shared__ double s_mean[kRtChunk];   // and their means in fp32 arithmetic
+    __shared__ int s_slot[kRtChunk];      // candidate of the chunk -> its place in the list, -1 when ruled out
+    __shared__ float s_seg[kRtWaves][64];
+    __shared__ float s_rows[kRtWaves][4][64];
+    __shared__ int s_n;
+    const int lane = tid & 63, wave = tid >> 6;
+    double lo = INFINITY;
+    bool odd = false;
+    for (int k = tid; k < k_cand; k += kRtThreads) {
+      const double mean = mean_of(k);
+      if (scores) scores[n * k_cand + k] = (float)mean;
+      if (mean < lo) lo = mean;
+      odd = odd || !isfinite(mean);
+    }
+    sv[tid] = lo;
     __syncthreads();
+    for (int s = kRtThreads / 2; s > 0; s >>= 1) {
+      if (tid < s && sv[tid + s] < sv[tid]) sv[tid] = sv[tid + s];
+      __syncthreads();
+    }
+    const double low = sv[0];
+    s_rows[wave][3][lane] = 0.f;
+    __syncthreads();
+    const double limit = low + 2.0 * 0x1p-24 * (70.0 * (abs1 / (double)cnt) + 200.0 * low);
+    const bool none = !odd && lo > limit;  // none of this thread's candidates remains
+    const RtPair pr(rowf + (int64_t)kRtRow * n);
+    const bool cap = !isinf(tau);
+    const float tauf = cap ? (float)tau : 0.f;
+    for (int c0 = 0; c0 < k_cand; c0 += kRtChunk) {
+      if (tid == 0) s_n = 0;
+      __syncthreads();
+      const int ce = min(c0 + kRtChunk, k_cand);
+      for (int k = c0 + tid; k < ce; k += kRtThreads) {
+        int slot = -1;
+        if (!none && !(mean_of(k) > limit)) {
+          slot = atomicAdd(&s_n, 1);
+          s_list[slot] = k;
+          s_mean[slot] = 0.0;
+        }
+        s_slot[k - c0] = slot;
+      }
+      __syncthreads();
+      const int nc = s_n;
+      for (int b = 0; b < nc; b += 16) {
+        // 16 contenders at a time over runs of kRtRun matches, a segment per
+        // wave: the full segments' lane sums are added in order, then the
+        // last, shorter one's and the lanes' in fp64
+        const int kq = lane >> 4, mine = b + (lane & 15);
+        const float u = kq < 3 && mine < nc ? cand[(int64_t)kq * kp + s_list[mine]] : 0.f;
+        for (int m0 = 0; m0 < cnt; m0 += kRtRun) {
+          const int rc = min(kRtRun, cnt - m0), nblk = (rc + 15) >> 4;
+          s_seg[wave][lane] =
+              rt_segment_sum(pr, start + m0, rc, wave * kRtSeg, u, cap, tauf, lane, s_rows[wave], x1, y1, x2, y2);
+          __syncthreads();
+          if (wave == 0) {
+            float acc2 = 0.f;
+            const int full = nblk / kRtSeg;
+            for (int w = 0; w < full; ++w) acc2 += s_seg[w][lane];
+            const float accf = full < kRtWaves ? s_seg[full][lane] : 0.f;
+            double s = (double)acc2 + (double)accf;
+            s += __shfl_xor(s, 16);
+            s += __shfl_xor(s, 32);
+            if (lane < 16 && mine < nc) s_mean[mine] += (double)(float)s;
+          }
+          __syncthreads();
+        }
+      }
+      for (int k = c0 + tid; k < ce; k += kRtThreads) {
+        const int slot = s_slot[k - c0];
+        if (slot < 0) continue;
+        const double mean = s_mean[slot] / (double)cnt;
+        if (scores) scores[n * k_cand + k] = (float)mean;
+        if (bk < 0 || mean < bv) {
+          bv = mean;
+          bk = k;
+        }
+      }
+      __syncthreads();
+    }
   }
   sv[tid] = bv;
   si[tid] = bk;
@@ -759,50 +856,85 @@ hipError_t launch_rt_pairs(hipStream_t st, int64_t n_pairs, const int32_t* pair_
   return hipGetLastError();
 }
 
-template <bool CAP>
-hipError_t launch_rt_score_t(hipStream_t st, int64_t n_items, int n_groups, const int4* items, const float* rowf,
-                             const float* x1, const float* y1, const float* x2, const float* y2, const float* cand,
-                             int n_cand, int kp, float tau, float* partial, float* item_abs, hipEvent_t ev0,
-                             hipEvent_t ev1) {
+// Split products save products' time and cost the second scoring.  The
+// former, per (match, candidate): 98 fs with fp32 products, padded to a wave's
+// 256 candidates, 74 with split ones, to 128 (30M matches, 2,048 candidates:
+// 5.97 and 4.4 ms).  The latter, in a pair's workgroup: 2.2 us per chunk of
+// candidates and 1.6 us per run of kRtRun matches, all of it in sequence for the
+// longest pair, some 512 workgroups' worth at once over all pairs.  So a few
+// long pairs (one of 3M matches: 7.4 ms with fp32 products, 13.3 split), many
+// candidates of few matches (50,000 of 14,000 matches: 0.51 and 0.59 ms) and
+// small calls, where both are equal, take fp32 products.
+//
+// So does a cap below 2e-3 (1 px at 500 px): a mean's error bound grows with
+// |n|, its spread over the candidates with the cap's square, and where one
+// reaches the other every candidate is scored twice (2,000 outlier pairs of
+// 20,000 matches, 2,048 candidates, at a cap of 2e-3 8.5 ms either way, at
+// 1.4e-3 8.5 with fp32 products and 25.7 split).
+bool rt_split(int64_t n_pairs, int64_t n_matches, int64_t longest, int n_cand, double tau) {
+  if (!(tau >= 2e-3)) return false;
+  const auto padded = [&](int unit) { return (double)((n_cand + unit - 1) / unit * (int64_t)unit); };
+  const double saved = (double)n_matches * (98e-15 * padded(256) - 74e-15 * padded(128));
+  const double chunks = 2.2e-6 * (double)((n_cand + kRtChunk - 1) / kRtChunk);
+  const double run = 1.6e-6 / kRtRun;  // per match, whole runs
+  const double one = chunks + run * (double)((longest + kRtRun - 1) / kRtRun * kRtRun);
+  const double all = ((double)n_pairs * (chunks + run * kRtRun) + run * (double)n_matches) / 512;
+  return saved > std::max(one, all);
+}
+
+// `kernel` over the items, in slices that a grid holds, from item `first` on
+// with the rest of its arguments shifted by `shifted(first)`.
+template <class... Params, class Shift>
+hipError_t launch_rt_slices(hipStream_t st, void (*kernel)(Params...), int64_t n_items, int n_groups, hipEvent_t ev0,
+                            hipEvent_t ev1, Shift shifted) {
   const dim3 block(kRtThreads);
-  const int64_t most = grid_rows(n_groups, kRtThreads);  // items a launch takes
+  const int64_t most = grid_rows(n_groups, kRtThreads);
   hipError_t e = hipSuccess;
   for (int64_t i = 0; i < n_items && e == hipSuccess; i += most) {
     const int64_t n = std::min(most, n_items - i);
     const dim3 grid((unsigned)(n * n_groups));
-    if (ev0)
-      hipExtLaunchKernelGGL(k_rt_score<CAP>, grid, block, 0, st, i == 0 ? ev0 : nullptr,
-                            i + n == n_items ? ev1 : nullptr, 0, items + i, n_groups, rowf, x1, y1, x2, y2, cand, n_cand,
-                            kp, tau, partial + i * kp, item_abs + i);
-    else
-      k_rt_score<CAP><<<grid, block, 0, st>>>(items + i, n_groups, rowf, x1, y1, x2, y2, cand, n_cand, kp, tau,
-                                              partial + i * kp, item_abs + i);
+    std::apply(
+        [&](auto... a) {
+          if (ev0)
+            hipExtLaunchKernelGGL(kernel, grid, block, 0, st, i == 0 ? ev0 : nullptr, i + n == n_items ? ev1 : nullptr,
+                                  0, a...);
+          else
+            kernel<<<grid, block, 0, st>>>(a...);
+        },
+        shifted(i));
     e = hipGetLastError();
   }
   return e;
 }
 
-hipError_t launch_rt_score(hipStream_t st, int64_t n_items, int n_groups, const int4* items, const float* rowf,
-                           const float* x1, const float* y1, const float* x2, const float* y2, const float* cand,
-                           int n_cand, int kp, double tau, float* partial, float* item_abs, hipEvent_t ev0,
-                           hipEvent_t ev1) {
-  if (n_items == 0) return hipSuccess;
-  if (std::isinf(tau))
-    return launch_rt_score_t<false>(st, n_items, n_groups, items, rowf, x1, y1, x2, y2, cand, n_cand, kp, 0.f,
-                                    partial, item_abs, ev0, ev1);
-  return launch_rt_score_t<true>(st, n_items, n_groups, items, rowf, x1, y1, x2, y2, cand, n_cand, kp, (float)tau,
-                                 partial, item_abs, ev0, ev1);
+hipError_t launch_rt_score(hipStream_t st, bool split, int64_t n_items, int n_groups, const int4* items,
+                           const float* rowf, const float* x1, const float* y1, const float* x2, const float* y2,
+                           const float* cand, int n_cand, int kp, double tau, float* partial, float* item_abs,
+                           hipEvent_t ev0, hipEvent_t ev1) {
+  const bool cap = !std::isinf(tau);
+  const float tauf = cap ? (float)tau : 0.f;
+  if (split)
+    return launch_rt_slices(st, cap ? k_rt_score<true> : k_rt_score<false>, n_items, n_groups, ev0, ev1,
+                            [&](int64_t i) {
+                              return std::make_tuple(items + i, n_groups, rowf, x1, y1, x2, y2, cand, n_cand, kp, tauf,
+                                                     partial + i * kp, item_abs + i);
+                            });
+  return launch_rt_slices(st, cap ? k_rt_score32<true> : k_rt_score32<false>, n_items, n_groups, ev0, ev1,
+                          [&](int64_t i) {
+                            return std::make_tuple(items + i, n_groups, rowf, x1, y1, x2, y2, cand, n_cand, kp, tauf,
+                                                   partial + i * kp);
+                          });
 }
 
-hipError_t launch_rt_select(hipStream_t st, int64_t n_pairs, int k, int kp, double tau, const int32_t* pair_item_off,
-                            const int4* items, const float* partial, const float* item_abs, const float* cand,
-                            const float* rowf, const double* rowd, const float* x1, const float* y1, const float* x2,
-                            const float* y2, float* scores, int32_t* best, int32_t* vote, double* t_rel,
-                            double* score_best) {
+hipError_t launch_rt_select(hipStream_t st, bool split, int64_t n_pairs, int k, int kp, double tau,
+                            const int32_t* pair_item_off, const int4* items, const float* partial,
+                            const float* item_abs, const float* cand, const float* rowf, const double* rowd,
+                            const float* x1, const float* y1, const float* x2, const float* y2, float* scores,
+                            int32_t* best, int32_t* vote, double* t_rel, double* score_best) {
   if (n_pairs == 0) return hipSuccess;
-  k_rt_select<<<(unsigned)n_pairs, kRtThreads, 0, st>>>(k, kp, tau, pair_item_off, items, partial, item_abs, cand,
-                                                        rowf, rowd, x1, y1, x2, y2, scores, best, vote, t_rel,
-                                                        score_best);
+  const auto kernel = split ? k_rt_select<true> : k_rt_select<false>;
+  kernel<<<(unsigned)n_pairs, kRtThreads, 0, st>>>(k, kp, tau, pair_item_off, items, partial, item_abs, cand, rowf,
+                                                   rowd, x1, y1, x2, y2, scores, best, vote, t_rel, score_best);
   return hipGetLastError();
 }
 
