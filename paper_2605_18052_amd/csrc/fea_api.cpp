@@ -1008,6 +1008,16 @@ hipError_t structure_hash(fea_ctx* c, uint64_t* out) {
   return hipSuccess;
 }
 
+// The forms' 45 entries on the device while a checkpoint is written or read
+// (no buffer that captured steps hold: their generation stays).
+struct FormEntries {
+  double* p = nullptr;
+  hipError_t alloc(size_t bytes) { return hipMalloc(reinterpret_cast<void**>(&p), std::max<size_t>(bytes, 16)); }
+  ~FormEntries() {
+    if (p) (void)hipFree(p);
+  }
+};
+
 // Device arrays of the solver state, in checkpoint order, with their sizes in
 // the checkpoint (the forms take all their 45 entries there, 36 values on the
 // device).
@@ -2007,16 +2017,15 @@ fea_status fea_get_state(fea_ctx* c, void* buf, size_t* len) {
   h.prev_tau_px = c->prev_tau_px;
   uint8_t* w = static_cast<uint8_t*>(buf);
   put(w, &h, 1);
+  FormEntries forms;
   for (auto& sec : state_sections(c)) {
+    const void* src = sec.first->p;
     if (sec.first == &c->qW) {
-      constexpr fea::MonoTable mono;
-      std::vector<double> v;
-      HIP_OR_FAIL(c, download(c, v, c->qW, (size_t)c->P * fea::kMono));
-      for (int64_t n = 0; n < c->P; ++n)
-        for (int k = 0; k < fea::kQuad; ++k) put(w, &v[n * fea::kMono + mono.of[k]], 1);
-      continue;
+      HIP_OR_FAIL(c, forms.alloc(sec.second));
+      HIP_OR_FAIL(c, fea::launch_quad_spread(c, forms.p));
+      src = forms.p;
     }
-    HIP_OR_FAIL(c, hipMemcpyAsync(w, sec.first->p, sec.second, hipMemcpyDeviceToHost, c->stream));
+    HIP_OR_FAIL(c, hipMemcpyAsync(w, src, sec.second, hipMemcpyDeviceToHost, c->stream));
     w += sec.second;
   }
   const size_t S = c->S;
@@ -2076,17 +2085,15 @@ fea_status fea_set_state(fea_ctx* c, const void* buf, size_t len) {
   c->opt = h.opt;
   c->pcur = h.pcur;
   const uint8_t* r = static_cast<const uint8_t*>(buf) + sizeof(StateHdr);
+  FormEntries forms;
   for (auto& sec : state_sections(c)) {
+    void* dst = sec.first->p;
     if (sec.first == &c->qW) {
-      constexpr fea::MonoTable mono;
-      std::vector<double> v((size_t)c->P * fea::kMono);
-      for (int64_t n = 0; n < c->P; ++n)
-        for (int k = 0; k < fea::kQuad; ++k) take(r, &v[n * fea::kMono + mono.of[k]], 1);
-      HIP_OR_FAIL(c, upload(c, c->qW, v.data(), v.size()));
-      HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));  // v goes
-      continue;
+      HIP_OR_FAIL(c, forms.alloc(sec.second));
+      dst = forms.p;
     }
-    HIP_OR_FAIL(c, hipMemcpyAsync(sec.first->p, r, sec.second, hipMemcpyHostToDevice, c->stream));
+    HIP_OR_FAIL(c, hipMemcpyAsync(dst, r, sec.second, hipMemcpyHostToDevice, c->stream));
+    if (sec.first == &c->qW) HIP_OR_FAIL(c, fea::launch_quad_gather(c, forms.p));
     r += sec.second;
   }
   const size_t S = c->S;

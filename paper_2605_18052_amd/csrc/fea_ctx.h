@@ -223,6 +223,8 @@ hipError_t launch_quad_build(fea_ctx* c);
 hipError_t launch_mask_init(fea_ctx* c);
 hipError_t launch_mask_slots(fea_ctx* c, int32_t* slot_pos);
 hipError_t launch_quad_reduce(fea_ctx* c, const int32_t* pair_item_off_dev);
+hipError_t launch_quad_spread(fea_ctx* c, double* entries);
+hipError_t launch_quad_gather(fea_ctx* c, const double* entries);
 hipError_t launch_focal_update(fea_ctx* c);
 hipError_t launch_loss_sum(fea_ctx* c, double* out);
 hipError_t launch_judge(fea_ctx* c);

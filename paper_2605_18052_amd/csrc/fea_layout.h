@@ -61,9 +61,6 @@ constexpr int kMlpParams = kMlpHidden * kMlpFeat + kMlpHidden + kMlpHidden * kMl
 constexpr int64_t kMlpNoAllocMaxSamples = FEA_MLP_NOALLOC_MAX_SAMPLES;
 constexpr int tile_matches_of(int cfg) { return kTiles[cfg].threads * kVec * kTiles[cfg].steps; }
 
-// Device-side step counters, one slot per pose parity p (see the camera
-// kernel): Adam steps since the moments were zeroed, global steps, and the
-// running powers beta1^t, beta2^t of the bias corrections.
 // The quadratic form of a pair: a symmetric 9x9 matrix, whose 45 distinct
 // entries take 36 values.  With w = vec(p2 p1^T), entry (3a + b, 3a' + b') of
 // the sum of c w w^T is the sum of c (p2_a p2_a') (p1_b p1_b'), and each factor
@@ -75,16 +72,23 @@ constexpr int kMono = 36;
 // (0,8), (1,1), ...), the index 6 s + t of its value: entry (i, j) with
 // i = 3a + b, j = 3a' + b' is P2_{sym(a, a')} P1_{sym(b, b')}, where sym(a, a')
 // (0..5) is the index of the product x_a x_a', a <= a'.
+// And back, an entry that takes each value.
 struct MonoTable {
-  int of[kQuad];
+  int of[kQuad], entry[kMono];
   static constexpr int sym3(int a, int b) { return a > b ? sym3(b, a) : (a == 0 ? b : (a == 1 ? 2 + b : 5)); }
-  constexpr MonoTable() : of() {
+  constexpr MonoTable() : of(), entry() {
     int k = 0;
     for (int i = 0; i < 9; ++i)
-      for (int j = i; j < 9; ++j, ++k) of[k] = 6 * sym3(i / 3, j / 3) + sym3(i % 3, j % 3);
+      for (int j = i; j < 9; ++j, ++k) {
+        of[k] = 6 * sym3(i / 3, j / 3) + sym3(i % 3, j % 3);
+        entry[of[k]] = k;
+      }
   }
 };
 
+// Device-side step counters, one slot per pose parity p (see the camera
+// kernel): Adam steps since the moments were zeroed, global steps, and the
+// running powers beta1^t, beta2^t of the bias corrections.
 struct StepCounters {
   long long adam_t[2];
   long long global_t[2];

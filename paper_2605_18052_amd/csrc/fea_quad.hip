@@ -194,6 +194,22 @@ __global__ __launch_bounds__(kQuadThreads) void k_quad_build(
   }
 }
 
+// The forms' 45 entries from their 36 values, as checkpoints hold them, and
+// back.
+__constant__ constexpr MonoTable kMonoOf{};
+
+__global__ __launch_bounds__(kQuadThreads) void k_quad_spread(int64_t n, const double* __restrict__ qW,
+                                                              double* __restrict__ entries) {
+  const int64_t t = (int64_t)blockIdx.x * kQuadThreads + threadIdx.x;
+  if (t < n * kQuad) entries[t] = qW[t / kQuad * kMono + kMonoOf.of[t % kQuad]];
+}
+
+__global__ __launch_bounds__(kQuadThreads) void k_quad_gather(int64_t n, const double* __restrict__ entries,
+                                                              double* __restrict__ qW) {
+  const int64_t t = (int64_t)blockIdx.x * kQuadThreads + threadIdx.x;
+  if (t < n * kMono) qW[t] = entries[t / kMono * kQuad + kMonoOf.entry[t % kMono]];
+}
+
 // Every valid slot of the layout retained (start of a solve).  A thread takes
 // four slots with one load and one store (the layout is a multiple of kAlign
 // slots, both arrays are allocations of their own); with one slot each the
@@ -272,6 +288,21 @@ hipError_t launch_mask_slots(fea_ctx* c, int32_t* slot_pos) {
   const int64_t n = c->layout_len;
   if (n == 0) return hipSuccess;
   k_mask_slots<<<(unsigned)((n + 255) / 256), 256, 0, c->stream>>>(n, c->qmask.as<unsigned char>(), slot_pos);
+  return hipGetLastError();
+}
+
+// entries: [P * kQuad] on the device.
+hipError_t launch_quad_spread(fea_ctx* c, double* entries) {
+  if (c->P == 0) return hipSuccess;
+  k_quad_spread<<<(unsigned)((c->P * kQuad + kQuadThreads - 1) / kQuadThreads), kQuadThreads, 0, c->stream>>>(
+      c->P, c->qW.as<double>(), entries);
+  return hipGetLastError();
+}
+
+hipError_t launch_quad_gather(fea_ctx* c, const double* entries) {
+  if (c->P == 0) return hipSuccess;
+  k_quad_gather<<<(unsigned)((c->P * kMono + kQuadThreads - 1) / kQuadThreads), kQuadThreads, 0, c->stream>>>(
+      c->P, entries, c->qW.as<double>());
   return hipGetLastError();
 }
 
