@@ -668,7 +668,7 @@ fea_status fea_focal_vote(fea_ctx *ctx, int32_t n_cams, int64_t n_pairs, const i
  * Requires loaded matches (FEA_ESTATE otherwise); FEA_EINVAL for
  * n_cand outside [1, 2^22], candidates that are not unit vectors (1e-6) or
  * focal lengths <= 0 or tau_px <= 0; FEA_ENONFINITE for non-finite input.  Device scratch
- * (n_cand rounded up to 512, times the number of 2048-match work items, in
+ * (n_cand rounded up to 128 or 256, times the number of 2048-match work items, in
  * fp32) up to 256 MiB stays with the context, the rest is allocated and freed
  * by the call. */
 fea_status fea_relative_translations(fea_ctx *ctx, const double *R, const double *f, double tau_px, int32_t n_cand,

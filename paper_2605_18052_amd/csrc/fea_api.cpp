@@ -2703,7 +2703,8 @@ fea_status fea_relative_translations(fea_ctx* c, const double* R, const double* 
   const int64_t n_items = (int64_t)items.size();
   const int group = split ? fea::kRtGroup : fea::kRtGroup32;
   const int groups = (n_cand + group - 1) / group;
-  const int kp = groups * group;
+  const int unit = split ? fea::kRtWave : fea::kRtWave32;  // waves past the candidates leave
+  const int kp = (n_cand + unit - 1) / unit * unit;
   std::vector<float> cs((size_t)3 * kp, 0.f);  // structure of arrays, zero-padded
   for (int32_t k = 0; k < n_cand; ++k)
     for (int a = 0; a < 3; ++a) cs[(size_t)a * kp + k] = (float)cand[3 * (size_t)k + a];

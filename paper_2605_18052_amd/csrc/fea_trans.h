@@ -18,9 +18,11 @@ namespace fea {
 // (4 waves x kRtBlocks32 blocks of 16).
 constexpr int kRtItem = 2048;
 constexpr int kRtBlocks = 4;
-constexpr int kRtGroup = 4 * kRtBlocks * 32;
+constexpr int kRtWave = kRtBlocks * 32;  // candidates of one wave
+constexpr int kRtGroup = 4 * kRtWave;
 constexpr int kRtBlocks32 = 16;
-constexpr int kRtGroup32 = 4 * kRtBlocks32 * 16;
+constexpr int kRtWave32 = kRtBlocks32 * 16;
+constexpr int kRtGroup32 = 4 * kRtWave32;
 constexpr int kRtRow = 16;  // per-pair row: R_ij (9), 1/f_i, 1/f_j, cx_i, cy_i, cx_j, cy_j, pad
 
 // Adam state shared by all cameras of one alignment phase, one slot per step
@@ -37,7 +39,8 @@ hipError_t launch_rt_pairs(hipStream_t st, int64_t n_pairs, const int32_t* pair_
 // Whether a search of n_matches in n_pairs (the longest with `longest`) takes
 // split products or fp32 ones; tau in normalised units.
 bool rt_split(int64_t n_pairs, int64_t n_matches, int64_t longest, int n_cand, double tau);
-// partial [n_items * kp]: every candidate's (capped) sum over the item.  Split
+// partial [n_items * kp]: every candidate's (capped) sum over the item, kp the
+// candidates rounded up to a wave's.  Split
 // products also leave item_abs [n_items]: the sum of |n|_1 over the item's
 // matches, which bounds how far those sums are from fp32 products' (see
 // launch_rt_select).

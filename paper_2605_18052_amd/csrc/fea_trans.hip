@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kRtThreads) void k_rt_score(const int4* __restrict_
   if (grp == 0 && threadIdx.x == 0) item_abs[it] = (s_abs[0] + s_abs[1]) + (s_abs[2] + s_abs[3]);
 
   const int hf = lane >> 5, col = lane & 31;
-  const int cbase = grp * kRtGroup + wave * (kRtBlocks * 32);
+  const int cbase = grp * kRtGroup + wave * kRtWave;
   if (cbase >= n_cand) return;  // the whole wave: nothing but padding
   bf16x8 b01[kRtBlocks], b2[kRtBlocks];
 #pragma unroll
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kRtThreads) void k_rt_score32(const int4* __restric
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int kq = lane >> 4, col = lane & 15;
-  const int cbase = grp * kRtGroup32 + wave * (kRtBlocks32 * 16);
+  const int cbase = grp * kRtGroup32 + wave * kRtWave32;
   if (cbase >= n_cand) return;  // the whole wave: nothing but padding
   float bop[kRtBlocks32];
 #pragma unroll
@@ -874,7 +874,7 @@ hipError_t launch_rt_pairs(hipStream_t st, int64_t n_pairs, const int32_t* pair_
 bool rt_split(int64_t n_pairs, int64_t n_matches, int64_t longest, int n_cand, double tau) {
   if (!(tau >= 2e-3)) return false;
   const auto padded = [&](int unit) { return (double)((n_cand + unit - 1) / unit * (int64_t)unit); };
-  const double saved = (double)n_matches * (98e-15 * padded(256) - 74e-15 * padded(128));
+  const double saved = (double)n_matches * (98e-15 * padded(kRtWave32) - 74e-15 * padded(kRtWave));
   const double chunks = 2.2e-6 * (double)((n_cand + kRtChunk - 1) / kRtChunk);
   const double run = 1.6e-6 / kRtRun;  // per match, whole runs
   const double one = chunks + run * (double)((longest + kRtRun - 1) / kRtRun * kRtRun);
