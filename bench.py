@@ -69,7 +69,7 @@ BATCH_CONVERGE_DEG = 0.01
 KERNEL_SOURCES = ("paper_2605_18052_amd/csrc/fea_resgrad.hip", "paper_2605_18052_amd/csrc/fea_device.h",
                   "paper_2605_18052_amd/csrc/fea_layout.h")
 PMC_TRAFFIC = {
-    "sources_sha256": "b6ec73f6635b4c1701498eba2cb6574b968f139c4b53fc8d0baa75d0e2f1ca4a",
+    "sources_sha256": "56a0735f8d8172db39c4a966f64368041413ca3d1b4d5aaf8d86fb23079777d8",
     # retained matches per launch -> "matches x threads" -> fetched + written bytes
     "bytes_per_launch": {
         87275962: {  # traj3000_m100M, round 0
@@ -378,7 +378,7 @@ def translation_stages(sc, fastea, synth, n_cand, with_cpu, cap_px=8.0, cpu_pair
     focal = {"cameras": sc.n_cams, "pairs": int(len(pc)), "candidates": len(fcand), "tau": 0.05,
              "kernel": "k_fv_vote", "kernel_ms": float(np.median(f_ms)),
              "matrices_per_s": n_eval / (float(np.median(f_ms)) / 1e3),
-             "bound": "latency: one wave per (camera, 64 candidates), lanes over candidates, ~20 pairs each, fp64 closed-form 3x3",
+             "bound": "latency: one wave per (camera, 64 candidates), lanes over candidates, ~20 pairs each, fp64 forms of rank-2 matrices",
              "f_best_over_true_median": float(np.median(ratio)),
              "within_5pct": float(np.mean(np.abs(ratio - 1) < 0.05))}
     # global rotation on the same scene's pair graph: true relative rotations
@@ -401,7 +401,7 @@ def translation_stages(sc, fastea, synth, n_cand, with_cpu, cap_px=8.0, cpu_pair
                 "error_init_deg": metrics.mean_rotation_error_deg(ra["R_init"], sc.R_gt),
                 "error_deg": metrics.mean_rotation_error_deg(ra["R"], sc.R_gt),
                 "loss_init": ra["loss_init"], "loss": ra["loss"],
-                "bound": "latency: six launches per Lanczos step (operator, two projection and two "
+                "bound": "latency: five launches per Lanczos step (operator, two projection and two "
                          "subtraction passes, normalisation; host check every 16 steps) and one per Adam step, "
                          "O(pairs) fp64 each"}
     out = {"relative_translations": search, "alignment": align, "focal_vote": focal, "rotation": rotation}

@@ -631,9 +631,10 @@ fea_status fea_rotation_averaging(fea_ctx *ctx, int32_t n_cams, int64_t n_pairs,
  * with more than one group), cand_f [n_cand] > 0, tau > 0.  Outputs (host):
  * f_best [n_groups], k_best [n_groups] (nullable), votes
  * [n_groups*n_cand] (nullable), ms (nullable: the vote kernel's HIP-event
- * time).  fp64 throughout; the singular-value ratio comes from the closed-form
- * eigenvalues of E^T E, which fix it to ~1.5e-8 near equal values.  The
- * context only supplies device, stream and error message.  FEA_EINVAL for
+ * time).  fp64 throughout; the singular-value ratio of a matrix of rank 2 (a
+ * third singular value below ~1e-14 of the second) comes from 2x2 forms to
+ * rounding, that of any other from the closed-form eigenvalues of E^T E, which
+ * fix it to ~1.5e-8 near equal values.  The context only supplies device, stream and error message.  FEA_EINVAL for
  * invalid sizes, pairs, groups or values; FEA_ENONFINITE for a non-finite F. */
 fea_status fea_focal_vote(fea_ctx *ctx, int32_t n_cams, int64_t n_pairs, const int32_t *pair_i,
                           const int32_t *pair_j, const double *F, const int32_t *group, const double *f_cur,
@@ -657,7 +658,10 @@ fea_status fea_focal_vote(fea_ctx *ctx, int32_t n_cams, int64_t n_pairs, const i
  * with |eps| < tau at the chosen direction votes +1 when both depths of its
  * least-squares two-view triangulation with translation u are positive, -1
  * when both are negative, 0 otherwise; the result is u for a vote sum >= 0,
- * else -u.  Scores are fp32 on the matrix cores; the vote is fp64.  Inputs
+ * else -u.  Scores are fp32 sums of matrix-core products (fp32, or split bf16
+ * parts that carry as many bits, whichever is faster for the sizes; the chosen
+ * direction and its score are those of fp32 products either way); the vote is
+ * fp64.  Inputs
  * (host, copied): R [n_cams*9] world-to-camera rotations, f [n_cams] focal
  * lengths (NULL = the loaded intrinsics), tau_px > 0, cand [n_cand*3] unit
  * vectors (one hemisphere suffices).  Outputs (host, caller-allocated,

@@ -2485,8 +2485,10 @@ namespace {
 // pinned ring, neighbours in one copy.  A context's calls come one after
 // another on its stream, so one call's memory is free when the next begins.
 // Kept and staged against 13 to 28 allocations and pageable copies per call:
-// the focal vote of 500 cameras 233 -> 136 us, of 1,000 339 -> 226, the
-// candidate search of 30 million matches (86 MB of scratch) 5.11 -> 4.51 ms.
+// the focal vote of 500 cameras 233 -> 136 us, of 1,000 339 -> 220, the
+// candidate search of 30 million matches (86 MB of scratch) 5.11 -> 4.50 ms.
+// These hold from a context's second such call on; its first allocates the
+// blocks and the ring (500 cameras 250 us, 1,000 270 to 470, the search 6.1 ms).
 constexpr size_t kCallBlock = 4u << 20;
 constexpr size_t kCallKeep = 256u << 20;
 

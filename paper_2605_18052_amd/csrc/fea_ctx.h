@@ -101,7 +101,7 @@ struct fea_ctx {
   fea::DBuf item_keep, item_base;
   fea::DBuf pair_ws;     // int32: new lengths and offsets of the pairs while a layout is compacted
   fea::DBuf d_cam_code;  // int32 [2P]: per camera entry 2n + side
-  fea::DBuf item_rec;  // int4 per item: {pair, start, count, 0}
+  fea::DBuf item_rec;  // int4 per item: {pair, start, count, 1 where its scene has stopped}
   fea::DBuf d_scene_item_off;  // int32 [S+1]: items of each scene (contiguous)
   fea::DBuf scene_loss;        // double [S]
   bool scene_items_contiguous = true;  // each scene's items form one range

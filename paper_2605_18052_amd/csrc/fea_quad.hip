@@ -35,15 +35,15 @@ constexpr int kQuadThreads = 256;
 // workgroup, no block-level synchronisation): the threshold test at the
 // snapshot (|eps_hat| < tau, strict) of the matches the mask still holds,
 // the updated mask, the item's survivor count (and, with WEIGHTED, the sum
-// of the survivors' learned weights), and the 45 sums of c' w w^T over the
+// of the survivors' learned weights), and the 36 sums of c' P2_s P1_t over the
 // survivors with c' = 1/max(|eps_hat|, delta) times the learned weight on
 // learned scenes -- the 1/Z normaliser, known only once every item has been
 // counted, is applied when the items are summed into W_n.  The test is
 // branch-free: a dropped match gets c' = 0 and adds exactly zero.  Each lane
 // takes one match per trip, so only that match's products are live next to
-// the 36 per-lane sums (occupancy 4); the 36 sums are reduced over the wave
-// by three reduce-scatters (16, 16 and 4 sums), stored straight from the
-// lanes that hold them.
+// the 36 per-lane sums (4 waves per SIMD, with learned weights 3); the 36 sums
+// are reduced over the wave by three reduce-scatters (16, 16 and 4 sums),
+// stored straight from the lanes that hold them.
 //
 // What bounds it is the matches in flight: at 4 waves per SIMD and one trip
 // ahead 4.4 MB were under way, 3.4 TB/s.  kBuildDepth trips are loaded ahead

@@ -6,12 +6,13 @@
 // scalar triple product eps(u) = u . n with n = (R_ij x~1) x x~2, so a pair
 // with M matches and K candidates is the product of an M x 3 and a 3 x K
 // matrix followed by |.| and a sum over M: a dense contraction of depth 3.
-// It runs on the matrix cores with both factors split into bf16 parts that
-// carry fp32's 24 bits between them, |D| accumulated per lane in fp32; n is
-// computed once per match into LDS.  The candidates that come out lowest are
-// scored once more with fp32 products (v_mfma_f32_16x16x4f32), and the choice
-// is made among those.  A direction and its opposite score the same; the sign comes from a
-// cheirality vote (both triangulated depths positive) over the pair's matches.
+// It runs on the matrix cores, n computed once per match into LDS and |D|
+// accumulated per lane in fp32: in large searches with both factors split into
+// bf16 parts that carry fp32's 24 bits between them, the candidates that come
+// out lowest scored once more with fp32 products (v_mfma_f32_16x16x4f32) and the
+// choice made among those; else with fp32 products throughout (rt_split).  A
+// direction and its opposite score the same; the sign comes from a cheirality
+// vote (both triangulated depths positive) over the pair's matches.
 //
 // Camera centres.  The L1 direction loss of
 // Eq. fastmap-global-translation-objective is minimised with Adam, one thread
@@ -147,7 +148,7 @@ __device__ __forceinline__ bf16x8 match_operand(unsigned hm, unsigned ll) {
 // unused) held the vector unit up longer: the inner loop alone took 62.9
 // cycles per 256 products, against 41.0 (capped) and 33.1 (plain) in this
 // form; with 16x16x32 products 46.6, with 256 candidates per wave 86
-// (registers).  30M matches, 2,048 candidates, cap 8 px: 5,971 -> 4,406 us.
+// (registers).  30M matches, 2,048 candidates, cap 8 px: 5,971 -> 4,400 us.
 // The sums' error against fp64 is not above the fp32 products' (relative,
 // norm over all scores: 7.1e-8 for 1.8e-7 capped at 8 px, 4.8e-8 for 5.2e-8
 // uncapped).
@@ -649,7 +650,8 @@ __global__ __launch_bounds__(kTaThreads) void k_ta_entries(int n_cams, const int
 // x, y, z.  A chain of dependent loads (the camera's range, its entries, the
 // other cameras' centres) and fp64 roots: the camera is uniform over the
 // wave, so its own data arrives by scalar loads, and two trips' entries are
-// in flight together.  500 cameras of 125 pairs, 2 runs: 4.82 -> 4.2 us.
+// in flight together.  500 cameras of 125 pairs, 2 runs, 2,000 steps: 10.3 ->
+// 8.6-9.0 ms.
 __global__ __launch_bounds__(kTaThreads) void k_ta_step(int n_cams, int64_t n_pairs,
                                                         const int32_t* __restrict__ cam_off,
                                                         const int2* __restrict__ ent2,
