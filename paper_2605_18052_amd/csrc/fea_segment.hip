@@ -573,6 +573,12 @@ hipError_t segment_matches(fea_ctx* c, const float* x1, const float* y1, const f
 namespace {
 
 constexpr int kItThreads = 256;
+// A launch takes fewer than 2^32 threads, and a layout up to 2^31 / kAlign
+// pairs: a wavefront for each and two threads for its camera entries would be
+// more, so past kItPairBlocks workgroups the wavefronts take further pairs.
+constexpr int64_t kItPairBlocks = 1 << 23;
+constexpr int64_t kItMaxPairs = (int64_t(1) << 31) / kAlign;
+static_assert((kItPairBlocks + 2 * kItMaxPairs / kItThreads + 1) * kItThreads < int64_t(1) << 32, "one launch");
 
 // The tables of a layout from its pairs' runs: the first pair_blocks
 // workgroups, one wavefront per pair, write the work items (runs of at most
@@ -587,13 +593,14 @@ __global__ __launch_bounds__(kItThreads) void k_items(
     int4* __restrict__ items, const int32_t* __restrict__ cam_code, const int32_t* __restrict__ pair_i,
     const int32_t* __restrict__ pair_j, int4* __restrict__ cam_ent) {
   if ((int)blockIdx.x < pair_blocks) {
-    const int n = blockIdx.x * (kItThreads / 64) + (threadIdx.x >> 6);
-    if (n >= P) return;
-    const int b = first[n], e = first[n + 1], s = start[n], l = len[n];
-    const int flag = done != nullptr && done[pair_scene[n]] != 0 ? 1 : 0;
-    for (int it = b + (threadIdx.x & 63); it < e; it += 64) {
-      const int at = (it - b) * tile;
-      items[it] = make_int4(n, s + at, min(tile, l - at), flag);
+    constexpr int kWaves = kItThreads / 64;
+    for (int n = blockIdx.x * kWaves + (threadIdx.x >> 6); n < P; n += pair_blocks * kWaves) {
+      const int b = first[n], e = first[n + 1], s = start[n], l = len[n];
+      const int flag = done != nullptr && done[pair_scene[n]] != 0 ? 1 : 0;
+      for (int it = b + (threadIdx.x & 63); it < e; it += 64) {
+        const int at = (it - b) * tile;
+        items[it] = make_int4(n, s + at, min(tile, l - at), flag);
+      }
     }
     return;
   }
@@ -652,7 +659,7 @@ unsigned pair_waves(int64_t P) { return (unsigned)((P + kItThreads / 64 - 1) / (
 hipError_t launch_items(fea_ctx* c, bool flags) {
   const int64_t P = c->P;
   if (P == 0) return hipSuccess;
-  const unsigned pair_blocks = pair_waves(P);
+  const unsigned pair_blocks = (unsigned)std::min<int64_t>(pair_waves(P), kItPairBlocks);
   const int32_t* runs = c->pair_runs.as<int32_t>();
   k_items<<<pair_blocks + (unsigned)((2 * P + kItThreads - 1) / kItThreads), kItThreads, 0, c->stream>>>(
       (int)P, (int)pair_blocks, (int)tile_matches_of(c->tile_cfg), runs, runs + P + 1, runs + 2 * P + 1,
