@@ -861,26 +861,33 @@ hipError_t launch_rt_pairs(hipStream_t st, int64_t n_pairs, const int32_t* pair_
 // Split products save products' time and cost the second scoring.  The
 // former, per (match, candidate): 98 fs with fp32 products, padded to a wave's
 // 256 candidates, 74 with split ones, to 128 (30M matches, 2,048 candidates:
-// 5.97 and 4.4 ms).  The latter, in a pair's workgroup: 2.2 us per chunk of
-// candidates and 1.6 us per run of kRtRun matches, all of it in sequence for the
-// longest pair, some 512 workgroups' worth at once over all pairs.  So a few
-// long pairs (one of 3M matches: 7.4 ms with fp32 products, 13.3 split), many
-// candidates of few matches (50,000 of 14,000 matches: 0.51 and 0.59 ms) and
-// small calls, where both are equal, take fp32 products.
+// 5.97 and 4.4 ms); and 23 ns per match of the longest item, the chain that a
+// small call waits for (28 pairs of 2,800 matches 117 and 73 us).  The latter,
+// in a pair's workgroup: 1.3 us per chunk of candidates and 4.4 us per run of
+// kRtRun matches (a segment's part of it where the run is shorter), more with
+// the contenders that many candidates leave; all of it in sequence for the
+// longest pair, some 768 workgroups' worth at once over all pairs.  So fp32
+// products are for a few long pairs (one of 3M matches: 7.0 and 13.3 ms), many
+// candidates of few matches (4M of 14,000: 34 and 43.7 ms) and pairs of a few
+// dozen matches (1,225 of 50: 72 and 75 us).  Over 1 to 1,225 pairs of 50 to
+// 60,000 matches and 1 to 8,192 candidates the choice is within 4% of the
+// better one.
 //
-// So does a cap below 2e-3 (1 px at 500 px): a mean's error bound grows with
-// |n|, its spread over the candidates with the cap's square, and where one
-// reaches the other every candidate is scored twice (2,000 outlier pairs of
-// 20,000 matches, 2,048 candidates, at a cap of 2e-3 8.5 ms either way, at
-// 1.4e-3 8.5 with fp32 products and 25.7 split).
+// A cap below 2e-3 (1 px at 500 px) takes fp32 products too: a mean's error
+// bound grows with |n|, its spread over the candidates with the cap's square,
+// and where one reaches the other every candidate is scored twice (2,000
+// outlier pairs of 20,000 matches, 2,048 candidates, at a cap of 2e-3 8.5 ms
+// either way, at 1.4e-3 8.5 with fp32 products and 25.7 split).
 bool rt_split(int64_t n_pairs, int64_t n_matches, int64_t longest, int n_cand, double tau) {
   if (!(tau >= 2e-3)) return false;
+  const double P = (double)n_pairs, M = (double)n_matches, L = (double)longest;
   const auto padded = [&](int unit) { return (double)((n_cand + unit - 1) / unit * (int64_t)unit); };
-  const double saved = (double)n_matches * (98e-15 * padded(kRtWave32) - 74e-15 * padded(kRtWave));
-  const double chunks = 2.2e-6 * (double)((n_cand + kRtChunk - 1) / kRtChunk);
-  const double run = 1.6e-6 / kRtRun;  // per match, whole runs
-  const double one = chunks + run * (double)((longest + kRtRun - 1) / kRtRun * kRtRun);
-  const double all = ((double)n_pairs * (chunks + run * kRtRun) + run * (double)n_matches) / 512;
+  const double saved = M * (98e-15 * padded(kRtWave32) - 74e-15 * padded(kRtWave)) + 23e-9 * std::min(L, (double)kRtItem);
+  const double chunks = 1.3e-6 * (double)((n_cand + kRtChunk - 1) / kRtChunk);
+  const double run = 4.4e-6 * (1.0 + n_cand / 16384.0);
+  const double segment = (double)kRtRun / kRtWaves, full = std::floor(L / kRtRun);
+  const double one = chunks + run * (full + std::min((L - full * kRtRun) / segment, 1.0));
+  const double all = (P * chunks + run * std::min(P + M / kRtRun, M / segment)) / 768;
   return saved > std::max(one, all);
 }
 
